@@ -128,8 +128,8 @@ dect_status dect_project_noalloc(const dect_plan* plan, const void* img, void* s
  * ray geometry in a different but equivalent arithmetic form (so the pair is
  * adjoint to rounding: <R x, y> = <x, R^T y> to 1e-12 relative in FP64).
  * sino: device [n_views][n_det][ch]; img: device [ny][nx][ch] (overwritten);
- * ch in {1, 2, 4}.  async.  On a quarter-turn symmetric plan one or two channels
- * are first reordered into a plan-owned scratch sinogram, so calls with one plan
+ * ch in {1, 2, 4}.  async.  On a quarter-turn symmetric plan the sinogram is
+ * first reordered into a plan-owned scratch sinogram, so calls with one plan
  * must not run concurrently on different streams. */
 dect_status dect_backproject(const dect_plan* plan, const void* sino, void* img, int ch,
                              void* stream);
@@ -349,7 +349,8 @@ dect_status dect_lmcg_iterate(const dect_plan* plan, const void* m_h, const void
 /* ----------------------------------------------------------- autotuning --- */
 
 /* Launch shapes of the ADMM's transposed projector and projector:
- *  - bp_waves: waves of a transpose workgroup, splitting the views (2, 4 or 8);
+ *  - bp_waves: waves of a transpose workgroup, splitting the views (2, 4 or 8; images of few
+ *    pixel blocks run more, up to 16, so that the device is filled);
  *  - proj_waves: waves of a projector workgroup, splitting the lines its rays cross
  *    (2, 4 or 8);
  *  - proj_views: base views whose rays share a projector wave (1, 2, 4 or 8; the wave

@@ -94,7 +94,6 @@ struct dect_plan {
     // Rotational symmetry order (4: views v + k V/4 are quarter turns of base
     // view v; 1: none) and the number of base views Vb = V / sym.
     int sym = 1, Vb = 0;
-    double margin = 0.05;   // footprint margin of the transpose, in bins
     // Workgroup shapes of the ADMM transpose (waves splitting the views) and
     // projector (waves splitting the lines): 2, 4 or 8, set by dect_plan_tune.
     int bp_waves = 4, pj_waves = 8;
@@ -104,7 +103,8 @@ struct dect_plan {
     // device tables
     void* rays = nullptr;   // RayParam<T>[Vb * D]
     void* views = nullptr;  // ViewParam<T>[Vb]
-    void* bp_rays = nullptr;  // BpRay<T>[Vb * D]: the transpose's form of the rays
+    int* bp_order = nullptr;  // [bp_blocks]: the transpose's blocks in launch order (bp_block_order)
+    void* bp_rays = nullptr;  // BpRay<T>[Vb][D + 1]: the transpose's form of the rays, a zero record at each row's end
     void* spec = nullptr;   // T[6 * Kmax]: lw_h, kc_h, kp_h, lw_l, kc_l, kp_l
     int kh = 0, kl = 0, kmax = 0;
     // Both spectra on one energy grid, for evaluating them with one exponential per
@@ -124,7 +124,7 @@ struct dect_plan {
     // plan-owned scratch: orbit images of the image being projected (up to 4 channels)
     void* scratch_O = nullptr;   // T[N * 4 * sym]
     void* scratch_OT = nullptr;  // T[N * 4 * sym]
-    void* scratch_sq = nullptr;  // sym == 4: T[Vb][D][4][2], a sinogram as quad records
+    void* scratch_sq = nullptr;  // sym == 4: T[Vb][D][4][4], a sinogram of up to 4 channels as quad records
     // preconditioner of the x-update (ramp filter on a zero-padded FFT grid of
     // px x py = 2^lpx x 2^lpy; absent when a padded side exceeds kMaxFft)
     bool has_precond = false;

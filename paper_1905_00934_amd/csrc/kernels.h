@@ -113,7 +113,7 @@ struct BpArgs {
     const ViewParam<T>* views;
     int nx, ny, V, Vb, D;
     int gx, gy;   // this slice's grid of 8x8 orbit blocks
-    double margin;
+    const int* order;  // [gx gy]: the block of each launch position (bp_block_order)
     const T* sino;
     T* out;
     T* out2;

@@ -1,5 +1,6 @@
 // Plan creation: geometry validation, Joseph ray tables, per-view footprint
 // tables, spectral tables and the per-slice state layout.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -100,12 +101,15 @@ dect_status build_tables(dect_plan* p, const dect_spectra* spec) {
     }
     dect_status st = upload<T>(rays.data(), rays.size() * sizeof(rays[0]), &p->rays);
     if (st) return st;
-    std::vector<BpRay<T>> brays(rays.size());
-    for (size_t k = 0; k < rays.size(); ++k) {
-        const RayParam<T>& r = rays[k];
-        const bool xs = r.pad == T(0);
-        brays[k] = BpRay<T>{r.phi0, xs ? r.slope : T(-1), xs ? T(-1) : r.slope, r.step};
-    }
+    // The transpose's rows end in a zero record, which a bin off the detector reads.
+    std::vector<BpRay<T>> brays((size_t)V * (D + 1), BpRay<T>{});
+    for (int v = 0; v < V; ++v)
+        for (int b = 0; b < D; ++b) {
+            const RayParam<T>& r = rays[(size_t)v * D + b];
+            const bool xs = r.pad == T(0);
+            brays[(size_t)v * (D + 1) + b] =
+                BpRay<T>{r.phi0, xs ? r.slope : T(-1), xs ? T(-1) : r.slope, r.step};
+        }
     st = upload<T>(brays.data(), brays.size() * sizeof(brays[0]), &p->bp_rays);
     if (st) return st;
     st = upload<T>(views.data(), views.size() * sizeof(views[0]), &p->views);
@@ -195,8 +199,33 @@ dect_status build_tables(dect_plan* p, const dect_spectra* spec) {
     }
     DECT_HIP(hipMalloc(&p->scratch_O, (size_t)p->N * 4 * p->sym * sizeof(T)));
     DECT_HIP(hipMalloc(&p->scratch_OT, (size_t)p->N * 4 * p->sym * sizeof(T)));
-    if (p->sym == 4) DECT_HIP(hipMalloc(&p->scratch_sq, (size_t)p->M * 2 * sizeof(T)));
+    if (p->sym == 4) DECT_HIP(hipMalloc(&p->scratch_sq, (size_t)p->M * 4 * sizeof(T)));
     return DECT_OK;
+}
+
+// Launch order of the transpose's 8x8 orbit blocks.  A block's work grows with its
+// distance from the rotation centre (the views that see it from near the source spread it
+// over more bins), and at the usual sizes every workgroup of a launch is resident at once,
+// so a compute unit finishes when the workgroups it was dealt do: row-major order dealt some
+// of them four edge blocks.  The blocks are sorted by distance, farthest first, and every
+// other run of kCus of them is reversed, so that the units' shares balance.
+dect_status build_block_order(dect_plan* p) {
+    constexpr int kCus = 256;
+    const int dx = p->sym == 4 ? p->nx / 2 : p->nx, dy = p->sym == 4 ? p->ny / 2 : p->ny;
+    const int gx = (dx + 7) / 8, n = bp_blocks(p);
+    std::vector<int> order(n);
+    std::vector<double> r2(n);
+    for (int t = 0; t < n; ++t) {
+        const double x = (t % gx) * 8 + 3.5 - 0.5 * (p->nx - 1);
+        const double y = (t / gx) * 8 + 3.5 - 0.5 * (p->ny - 1);
+        r2[t] = x * x + y * y;
+        order[t] = t;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return r2[a] > r2[b]; });
+    for (int a = kCus; a < n; a += 2 * kCus)
+        std::reverse(order.begin() + a, order.begin() + std::min(a + kCus, n));
+    return upload<int>(order.data(), order.size() * sizeof(int),
+                       reinterpret_cast<void**>(&p->bp_order));
 }
 
 // Smallest power of two at least twice n (linear convolution over the image).
@@ -437,23 +466,12 @@ dect_status dect_plan_create(const dect_geometry* geom, const dect_spectra* spec
                  ? 4
                  : 1;
     p->Vb = g.n_views / p->sym;
-    // Footprint margin of the transpose: the detector coordinate of the two-pixel
-    // segment around a pixel is linearised at its centre; for a fan the error is at
-    // most |d beta| * pixel / (distance to source - pixel).  Plus 0.02 bins for
-    // rounding of the tables and of the footprint itself.
-    p->margin = 0.02;
-    if (g.kind == DECT_FAN) {
-        const double rc = 0.5 * g.pixel_cm * std::hypot((double)g.nx, (double)g.ny);
-        const double dmin = g.src_iso_cm - rc - 2.0 * g.pixel_cm;
-        const double K = g.src_det_cm / g.det_cm;
-        const double dbeta = (K * g.pixel_cm + K * rc / dmin * g.pixel_cm) / dmin;
-        p->margin += 1.5 * dbeta * g.pixel_cm / (dmin - g.pixel_cm);
-    }
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
         return fail(DECT_E_DEVICE, "no HIP device");
     }
     dect_status st = dtype == DECT_F32 ? build_tables<float>(p, spec) : build_tables<double>(p, spec);
+    if (st == DECT_OK) st = build_block_order(p);
     if (st == DECT_OK) st = dtype == DECT_F32 ? build_precond<float>(p) : build_precond<double>(p);
     if (st == DECT_OK) st = dtype == DECT_F32 ? build_fbp<float>(p) : build_fbp<double>(p);
     if (st == DECT_OK && hipMalloc(reinterpret_cast<void**>(&p->scratch_part),
@@ -475,6 +493,7 @@ void dect_plan_destroy(dect_plan* p) {
     (void)hipFree(p->rays);
     (void)hipFree(p->views);
     (void)hipFree(p->bp_rays);
+    (void)hipFree(p->bp_order);
     (void)hipFree(p->spec);
     (void)hipFree(p->joint);
     (void)hipFree(p->scratch_O);

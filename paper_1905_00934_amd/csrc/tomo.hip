@@ -15,8 +15,7 @@
 // rays cross in LDS and its lanes read their taps from there.
 //
 // Transpose: one lane owns the rotation orbit of a pixel.  For every base view
-// and every orbit member it locates, from the central projection of the
-// two-pixel segment around the pixel, the bins whose samples can touch it, and
+// and every orbit member it locates the bins whose samples can touch the pixel and
 // re-evaluates each candidate's interpolation weight from the same ray geometry;
 // each weight serves SYM (pixel, view) pairs.  The projector forms the two tap
 // weights of a sample as tents max(0, 1 - |phi - j|) and scales by the step length at
@@ -26,6 +25,7 @@
 // of a workgroup and the wave sums are added in a fixed order through LDS.
 #include <mutex>
 
+#include "bpidx.h"
 #include "common.h"
 #include "epilogue.h"
 #include "kernels.h"
@@ -401,430 +401,381 @@ __device__ inline T fast_rcp(T x) { return T(1) / x; }
 template <>
 __device__ inline float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// Sum over the base views of this wave (v = wave, wave + VS, ...) for the orbit
-// of pixel (i, j), reading a standard [V][D][CH] sinogram.  Pixel rot^k(p) seen
-// from view v + k' Vb has the weight of base view v at pixel rot^(k - k')(p), so
-// for every orbit member p_m = rot^m(p) the base-view weights are evaluated once
-// and routed to acc[(m + k') mod SYM] with sinogram row v + k' Vb, for all k'.
+// The transposed gather of one wave: an 8x8 block of pixel orbits, one orbit per lane.
 //
-// Candidates are the bins within h = max|d beta / d pixel| + margin of the
-// member's detector coordinate beta (a ray more than one pixel step away along
-// its minor axis has no tap on the pixel); the footprint needs only ~1e-3-bin
-// accuracy, which the margin covers, hence the hardware reciprocal.  The ray's
-// type says which pixel coordinate it samples along, and the weight
-// max(0, step (1 - |phi - p|)) is the projector's linear-interpolation weight of
-// the pixel at minor coordinate p for the sample at phi, phi computed with the
-// same fma on the same table entries as the projector's sample position.
-template <typename T, typename A, int CH, int SYM, int VS>
-__device__ inline void gather_orbit(const BpArgs<T>& a, int wave, int i, int j,
-                                    A (&acc)[SYM][CH]) {
-    const T m = (T)a.margin;
-    const int D = a.D, Vb = a.Vb, n = a.nx;
-    const T cx = T(0.5) * (T)(a.nx - 1), cy = T(0.5) * (T)(a.ny - 1);
-    const vec<T, CH>* __restrict__ sv = reinterpret_cast<const vec<T, CH>*>(a.sino);
-    for (int v = wave; v < Vb; v += VS) {
-        const ViewParam<T> w = a.views[v];
-        const RayParam<T>* __restrict__ rv = a.rays + (size_t)v * D;
-#pragma unroll
-        for (int mm = 0; mm < SYM; ++mm) {
-            int im, jm;
-            rot(mm, n, i, j, im, jm);
-            const T fi = (T)im, fj = (T)jm;
-            const T ip = fi - cx, jp = fj - cy;
-            const T inv = fast_rcp<T>(w.d0 + w.di * ip + w.dj * jp);
-            const T bq = (w.ni * ip + w.nj * jp) * inv;
-            const T bc = bq + w.boff;
-            // d(beta) for one pixel step along y and along x.
-            const T dby = (w.nj - bq * w.dj) * inv;
-            const T dbx = (w.ni - bq * w.di) * inv;
-            const T h = fmax(fabs(dby), fabs(dbx)) + m;
-            const int lo0 = (int)ceil(fmax(bc - h, T(-1)));
-            const int hi0 = (int)floor(fmin(bc + h, T(D)));
-            const int lo = lo0 > 0 ? lo0 : 0, hi = hi0 < D - 1 ? hi0 : D - 1;
-            for (int b = lo; b <= hi; ++b) {
-                const RayParam<T> r = rv[b];
-                const bool xs = r.pad == T(0);
-                const T phi = fma(r.slope, xs ? fi : fj, r.phi0);
-                const T wt = fmax(T(0), fma(-r.step, fabs(phi - (xs ? fj : fi)), r.step));
-#pragma unroll
-                for (int kp = 0; kp < SYM; ++kp) {
-                    const vec<T, CH> t = sv[(size_t)(v + kp * Vb) * D + b];
-#pragma unroll
-                    for (int c = 0; c < CH; ++c)
-                        acc[(mm + kp) % SYM][c] = fma((A)wt, (A)t.v[c], acc[(mm + kp) % SYM][c]);
-                }
-            }
-        }
-    }
-}
+// Pixel rot^k(p) seen from view v + k' Vb has the weight of base view v at pixel
+// rot^(k - k')(p), so for every orbit member p_m = rot^m(p) the base-view weights are
+// evaluated once and routed to acc[(m + k') mod SYM] with the sinogram value of view
+// v + k' Vb, for all k'.
+//
+// Candidates of a pixel are the bins within h of its detector coordinate beta, h the largest
+// change of beta over one pixel along an axis (a ray more than one pixel step away along its minor axis has
+// no tap on the pixel); the weight max(0, step (1 - |d|)) of a candidate, d its signed
+// minor-axis distance, is the projector's linear-interpolation weight.
+//
+// Per view and member ("slot") the block's candidates lie in a window of kBpWin bins.
+// The window, and where each pixel's candidates start in it, come from one plane per
+// slot: beta is projective in the pixel, beta - beta0 = (g.t) / (1 + e.t) with t the
+// offset from the block's centre, g its gradient there and e the relative gradient of the
+// denominator, so an affine beta is off by at most
+//   E = |t|^2 / 2 (|g||e| + |g.e|) / (1 - q),  q = max|e.t|,
+// and h by no more than the bound hb formed in bp_slot.  Each pixel then takes the C =
+// ceil(2 hb + 2 E) bins from floor(plane) + 1 on: all its candidates are among them, the
+// others have weight exactly zero, and C is the same for the whole wave.  The planes of
+// kBpBatch slots at a time are formed by the wave's lanes (one each) and kept in LDS, so a
+// pixel spends four instructions per slot on its footprint instead of about thirty.
+//
+// The windows of kBpSlots slots are staged at once, one record (ray record and the SYM *
+// CH sinogram values of the bin) per lane, the next group's loads in flight while the
+// current one is summed.  A record is held in 16-byte pieces, each piece an array of its
+// own, so that lanes reading neighbouring records never meet on a bank.
+//
+// A slot whose window would be too long (a block so near the source that the fan spreads
+// over more than kBpWin bins), and every slot of a wave whose sums came out non-finite
+// (zero weights must not carry a NaN or an infinity of the sinogram to other pixels), is
+// gathered candidate by candidate from global memory.
+//
+// What bounds it: LDS and VALU issue, about equally.  Per view and 64 pixels at
+// 512^2 / 720 x 1024 (two channels, FP32) 204 VALU instructions (341 with a footprint per
+// pixel, which took 62.9 M per launch against 37.2 M) and 46 LDS instructions of which the
+// 34 candidate reads take 4.6 cycles each and the 6 staging writes 13.8 (measured alone).
+// A launch takes 106-108 us (118-122 us before, at 4 waves per workgroup, 110-114 at 8);
+// 31 us at 256^2 (58 and 38); a plain one-channel transpose of 350 x 301 pixels over 451 x 481
+// parallel rays 47 us (97).
+constexpr int kBpSlots = 2;
+constexpr int kBpBatch = 64;
 
-// Quarter turns of a real point about the image centre, as rot() for pixels.
-template <typename T>
-__device__ inline void rotf(int k, int n, T i, T j, T& io, T& jo) {
-    const T e = (T)(n - 1);
-    switch (k & 3) {
-        case 0: io = i; jo = j; break;
-        case 1: io = e - j; jo = i; break;
-        case 2: io = e - i; jo = e - j; break;
-        default: io = j; jo = e - i; break;
-    }
-}
-
-// As gather_orbit for quad sinograms, with each view's candidate records staged in
-// LDS.  A wave covers the 64 orbits of its block: per view and orbit member their
-// candidate bins lie within a few bins of the block centre's detector coordinate,
-// so WIN records around it (ray parameters and the quad of sinogram values) are
-// loaded once per view by WIN lanes and read by every lane from LDS instead of
-// each lane loading them again.  The loads for the wave's next view are issued
-// before the current view is accumulated, so their latency is hidden.  A candidate
-// outside the window (a steep footprint near the source) is loaded directly.
-template <typename T, typename A, int CH, int SYM, int VS>
-__device__ inline void gather_orbit_staged(const BpArgs<T>& a, int wave, int lane, int i, int j,
-                                           int bx, int by, bool inside, A (&acc)[SYM][CH]) {
-    constexpr int WIN = 16;
-    using Q = vec<T, SYM * CH>;
-    __shared__ RayParam<T> s_ray[VS][WIN * SYM];
-    __shared__ Q s_sino[VS][WIN * SYM];
-    const T m = (T)a.margin;
-    const int D = a.D, Vb = a.Vb, n = a.nx;
-    const T cx = T(0.5) * (T)(a.nx - 1), cy = T(0.5) * (T)(a.ny - 1);
-    const Q* __restrict__ sino = reinterpret_cast<const Q*>(a.sino);
-    // This lane stages bin sk of the window of orbit member sm, centred on the
-    // detector coordinate of the block centre seen as that member.
-    const int sm = lane / WIN, sk = lane % WIN;
-    const bool stager = lane < WIN * SYM;
-    T icm, jcm;
-    rotf<T>(sm, n, (T)(bx * 8) + T(3.5), (T)(by * 8) + T(3.5), icm, jcm);
-    const T ipc = icm - cx, jpc = jcm - cy;
-    RayParam<T> pr{};
-    Q pq;
-    int pL = 0;
-    auto stage = [&](int v) {
-        const ViewParam<T> w = a.views[v];
-        const T bq = (w.ni * ipc + w.nj * jpc) / (w.d0 + w.di * ipc + w.dj * jpc);
-        pL = (int)floor(bq + w.boff) - (WIN / 2 - 1);
-        const int b = pL + sk;
-        if (stager && b >= 0 && b < D) {
-            pr = a.rays[(size_t)v * D + b];
-            pq = sino[(size_t)v * D + b];
-        } else {
-            pr = RayParam<T>{};
-#pragma unroll
-            for (int c = 0; c < SYM * CH; ++c) pq.v[c] = T(0);
-        }
-    };
-    if (wave < Vb) stage(wave);
-    for (int v = wave; v < Vb; v += VS) {
-        int L[SYM];
-#pragma unroll
-        for (int mm = 0; mm < SYM; ++mm) L[mm] = __builtin_amdgcn_readlane(pL, mm * WIN);
-        if (stager) {
-            s_ray[wave][lane] = pr;
-            s_sino[wave][lane] = pq;
-        }
-        // LDS operations of one wave complete in order; the barrier only keeps the
-        // compiler from moving the reads above the writes.
-        __builtin_amdgcn_wave_barrier();
-        if (v + VS < Vb) stage(v + VS);
-        if (inside) {
-            const ViewParam<T> w = a.views[v];
-            const RayParam<T>* __restrict__ rv = a.rays + (size_t)v * D;
-            const Q* __restrict__ sq = sino + (size_t)v * D;
-#pragma unroll
-            for (int mm = 0; mm < SYM; ++mm) {
-                int im, jm;
-                rot(mm, n, i, j, im, jm);
-                const T fi = (T)im, fj = (T)jm;
-                const T ip = fi - cx, jp = fj - cy;
-                const T inv = fast_rcp<T>(w.d0 + w.di * ip + w.dj * jp);
-                const T bq = (w.ni * ip + w.nj * jp) * inv;
-                const T bc = bq + w.boff;
-                const T dby = (w.nj - bq * w.dj) * inv;
-                const T dbx = (w.ni - bq * w.di) * inv;
-                const T h = fmax(fabs(dby), fabs(dbx)) + m;
-                const int lo0 = (int)ceil(fmax(bc - h, T(-1)));
-                const int hi0 = (int)floor(fmin(bc + h, T(D)));
-                const int lo = lo0 > 0 ? lo0 : 0, hi = hi0 < D - 1 ? hi0 : D - 1;
-                for (int b = lo; b <= hi; ++b) {
-                    const int idx = b - L[mm];
-                    RayParam<T> r;
-                    Q s;
-                    if ((unsigned)idx < (unsigned)WIN) {
-                        r = s_ray[wave][mm * WIN + idx];
-                        s = s_sino[wave][mm * WIN + idx];
-                    } else {
-                        r = rv[b];
-                        s = sq[b];
-                    }
-                    const bool xs = r.pad == T(0);
-                    const T phi = fma(r.slope, xs ? fi : fj, r.phi0);
-                    const T wt = fmax(T(0), fma(-r.step, fabs(phi - (xs ? fj : fi)), r.step));
-#pragma unroll
-                    for (int kp = 0; kp < SYM; ++kp)
-#pragma unroll
-                        for (int c = 0; c < CH; ++c)
-                            acc[(mm + kp) % SYM][c] =
-                                fma((A)wt, (A)s.v[kp * CH + c], acc[(mm + kp) % SYM][c]);
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// gather_orbit_staged with a 32-bin window for the quarter-turn symmetric fan: a
-// block's candidates span about 8 sqrt(2) pixels times the magnification
-// |d beta / d pixel| plus the footprint, ~14 bins at the centre of the fan and up to
-// ~35 for blocks near the source, so 16 bins left most waves loading some
-// candidates directly; with 32 that is rare.
-
-// A staged candidate of the wide window: its ray record and its quad of sinogram
-// values side by side (48 bytes for two FP32 channels), so that one address steps
-// through the window.
-template <typename T, int CH, int SYM>
-struct alignas(sizeof(T) * 4) Staged {
-    BpRay<T> r;
-    T s[SYM * CH];
+// Pieces of a staged record: the ray record in 16-byte pieces, the values in 16-byte
+// pieces or, below 16 bytes, in one piece of their size.
+template <typename T, int W>
+struct BpWindow {
+    static constexpr int PE = 16 / (int)sizeof(T);  // values per 16 bytes
+    static constexpr int RC = 4 / PE;               // pieces of a ray record
+    static constexpr int VE = W < PE ? W : PE;      // values per value piece
+    static constexpr int VC = W / VE;
+    vec<T, PE> ray[RC][kBpWin * kBpSlots];
+    vec<T, VE> val[VC][kBpWin * kBpSlots];
 };
-constexpr int kWideWin = 32;
-// Candidates every lane takes from its window before looping over the rest: most
-// footprints hold two or three, and a candidate past a pixel's footprint has weight
-// exactly zero (its ray passes more than a pixel step away), so the loop's control
-// flow is saved where most lanes need it least.  Each orbit member's window is
-// followed by kBpFixed zero records, so that those reads never leave it.
-#ifndef DECT_BP_FIXED
-#define DECT_BP_FIXED 0
-#endif
-constexpr int kBpFixed = DECT_BP_FIXED;
-constexpr int kWideStride = kWideWin + kBpFixed;
 
-// Each lane stages WIN * SYM / 64 records.  s_win: the workgroup's staging windows,
-// [VS][SYM members][kWideStride]; each wave uses only its own row.
 template <typename T, typename A, int CH, int SYM, int VS>
-__device__ inline void gather_orbit_staged_wide(const BpArgs<T>& a, int wave, int lane, int i, int j,
-                                                int bx, int by, bool inside, A (&acc)[SYM][CH],
-                                                Staged<T, CH, SYM> (*s_win)[kWideStride * SYM]) {
-    constexpr int WIN = kWideWin;
-    constexpr int REC = WIN * SYM;
-    constexpr int PER = (REC + 63) / 64;
-    static_assert(WIN % 16 == 0 && (REC <= 64 || REC % 64 == 0), "window layout");
-    static_assert(kBpFixed * SYM <= 64, "padding records per wave");
-    if constexpr (kBpFixed > 0) {
-        if (lane < kBpFixed * SYM) {  // the zero records after each window
-            Staged<T, CH, SYM>& z =
-                s_win[wave][(lane / kBpFixed) * kWideStride + WIN + lane % kBpFixed];
-            z.r = BpRay<T>{};
-#pragma unroll
-            for (int c = 0; c < SYM * CH; ++c) z.s[c] = T(0);
-        }
-    }
-    using Q = vec<T, SYM * CH>;
-    const T m = (T)a.margin;
+__device__ inline void gather_windows(const BpArgs<T>& a, int wave, int lane, int bx, int by,
+                                      BpWindow<T, CH * SYM>& win, BpSlot* slots,
+                                      A (&acc)[SYM][CH]) {
+    constexpr int W = CH * SYM;
+    using Win = BpWindow<T, W>;
+    // A group is kBpSlots slots staged together: SYM / kBpSlots groups per view, or one
+    // group of kBpSlots views.
+    constexpr int GPV = SYM == 4 ? SYM / kBpSlots : 1;  // groups per view step
+    constexpr int VPG = SYM == 4 ? 1 : kBpSlots;        // views per group
+    constexpr int SPV = GPV * kBpSlots;                 // slots per view step
+    constexpr int STEPS = kBpBatch / SPV;               // view steps per batch of slots
     const int D = a.D, Vb = a.Vb, n = a.nx;
-    const T cx = T(0.5) * (T)(a.nx - 1), cy = T(0.5) * (T)(a.ny - 1);
-    const Q* __restrict__ sino = reinterpret_cast<const Q*>(a.sino);
-    // Record lane + 64 q of the window is bin (rec % WIN) of orbit member rec / WIN,
-    // centred on the detector coordinate of the block centre seen as that member.
-    T ipc[PER], jpc[PER];
-    int sk[PER];
-    bool stager[PER];
+    const int i0 = bx * 8, j0 = by * 8;
+    const int i = i0 + (lane & 7), j = j0 + (lane >> 3);
+    const float oi = (float)(lane & 7), oj = (float)(lane >> 3);
+    using GC = const __attribute__((address_space(1))) char;
+
+    // A U at byte `off` of a row (uniform base, 32-bit offset).
+    auto load = [&](auto tag, const void* row, unsigned off) {
+        using U = decltype(tag);
+        using GU = const __attribute__((address_space(1))) U;
+        GU* q = (GU*)((GC*)row + off);
+        U o;
+        using GT = const __attribute__((address_space(1))) T;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int rec = lane + 64 * q;
-        stager[q] = rec < REC;
-        sk[q] = rec % WIN;
-        T icm, jcm;
-        rotf<T>(rec / WIN, n, (T)(bx * 8) + T(3.5), (T)(by * 8) + T(3.5), icm, jcm);
-        ipc[q] = icm - cx;
-        jpc[q] = jcm - cy;
-    }
-    BpRay<T> pr[PER];
-    Q pq[PER];
-    int pL[PER];
-    auto stage = [&](int v) {
-        const ViewParam<T> w = a.views[v];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            // Only the window's placement depends on this value (candidates outside
-            // it are loaded directly), so the hardware reciprocal is accurate enough.
-            const T bq = (w.ni * ipc[q] + w.nj * jpc[q]) *
-                         fast_rcp<T>(w.d0 + w.di * ipc[q] + w.dj * jpc[q]);
-            pL[q] = (int)floor(bq + w.boff) - (WIN / 2 - 1);
-            const int b = pL[q] + sk[q];
-            if (stager[q] && b >= 0 && b < D) {
-                pr[q] = a.brays[(size_t)v * D + b];
-                pq[q] = sino[(size_t)v * D + b];
-            } else {
-                pr[q] = BpRay<T>{};
-#pragma unroll
-                for (int c = 0; c < SYM * CH; ++c) pq[q].v[c] = T(0);
-            }
-        }
+        for (unsigned c = 0; c < sizeof(U) / sizeof(T); ++c)
+            reinterpret_cast<T*>(&o)[c] = ((GT*)q)[c];
+        return o;
     };
-    if (wave < Vb) stage(wave);
-    for (int v = wave; v < Vb; v += VS) {
-        int L[SYM];
+    auto ray_at = [&](int v, unsigned b) {
+        const BpRay<T>* row = a.brays + (size_t)v * (unsigned)(D + 1);
+        return load(BpRay<T>{}, row, b * (unsigned)sizeof(BpRay<T>));
+    };
+    // The values of bin b of base view v in all SYM views it stands for (a record).
+    auto values_at = [&](int v, unsigned b, T (&s)[W]) {
+        const vec<T, W> t = load(vec<T, W>{}, a.sino + (size_t)v * (unsigned)D * W,
+                                 b * (unsigned)sizeof(vec<T, W>));
 #pragma unroll
-        for (int mm = 0; mm < SYM; ++mm)
-            L[mm] = __builtin_amdgcn_readlane(pL[(mm * WIN) / 64], (mm * WIN) % 64);
+        for (int c = 0; c < W; ++c) s[c] = t.v[c];
+    };
+    // Record `lane` of the window written; record o read.
+    auto store = [&](const BpRay<T>& r, const T (&s)[W]) {
+        const T* rp = &r.phi0;
 #pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (stager[q]) {
-                const int rec = lane + 64 * q;
-                Staged<T, CH, SYM>& d = s_win[wave][(rec / WIN) * kWideStride + rec % WIN];
-                d.r = pr[q];
+        for (int h = 0; h < Win::RC; ++h)
 #pragma unroll
-                for (int c = 0; c < SYM * CH; ++c) d.s[c] = pq[q].v[c];
+            for (int c = 0; c < Win::PE; ++c) win.ray[h][lane].v[c] = rp[h * Win::PE + c];
+#pragma unroll
+        for (int h = 0; h < Win::VC; ++h)
+#pragma unroll
+            for (int c = 0; c < Win::VE; ++c) win.val[h][lane].v[c] = s[h * Win::VE + c];
+    };
+    auto fetch = [&](int o, BpRay<T>& r, T (&s)[W]) {
+        T* rp = &r.phi0;
+#pragma unroll
+        for (int h = 0; h < Win::RC; ++h)
+#pragma unroll
+            for (int c = 0; c < Win::PE; ++c) rp[h * Win::PE + c] = win.ray[h][o].v[c];
+#pragma unroll
+        for (int h = 0; h < Win::VC; ++h)
+#pragma unroll
+            for (int c = 0; c < Win::VE; ++c) s[h * Win::VE + c] = win.val[h][o].v[c];
+    };
+    auto weight = [&](const BpRay<T>& r, T fi, T fj) {
+        const T d = fma(r.ci, fi, fma(r.cj, fj, r.phi0));
+        return fmax(T(0), fma(-r.step, fabs(d), r.step));
+    };
+    // Base view of slot sl of view step t of this wave: view (SYM = 4) or kBpSlots
+    // consecutive views (SYM = 1) number wave, wave + VS, ...
+    auto view_of = [&](int t, int sl) {
+        return SYM == 4 ? wave + VS * t : (wave + VS * t) * VPG + sl;
+    };
+    const int nsteps = (Vb + VPG - 1) / VPG;
+    const int mine = nsteps > wave ? (nsteps - wave + VS - 1) / VS : 0;
+
+    int redo = 0;
+    for (;;) {
+        asm volatile("" : "+s"(redo));  // one loop body for both passes
+#pragma unroll 1
+        for (int t0 = 0; t0 < mine; t0 += STEPS) {
+            const int nt = mine - t0 < STEPS ? mine - t0 : STEPS;
+            unsigned long long left;
+            {  // this lane's slot of the batch
+                const int t = lane / SPV, sl = lane % SPV, v = view_of(t0 + t, sl);
+                BpSlot e{0.0f, 0.0f, 0.0f, 0};
+                if (t < nt && v < Vb) {
+                    e = bp_slot<SYM>(a.views[v], SYM == 4 ? sl : 0, i0, j0, n, a.ny, D);
+                    if (redo && (e.info & 255) != 0) e.info = kBpDirect;
+                }
+                left = __ballot((e.info & (kBpDirect | kBpLong)) != 0);
+                slots[lane] = e;
+                __builtin_amdgcn_wave_barrier();
             }
-        // LDS operations of one wave complete in order; the barrier only keeps the
-        // compiler from moving the reads above the writes.
-        __builtin_amdgcn_wave_barrier();
-        if (v + VS < Vb) stage(v + VS);
-        if (inside) {
-            const ViewParam<T> w = a.views[v];
-            const BpRay<T>* __restrict__ rv = a.brays + (size_t)v * D;
-            const Q* __restrict__ sq = sino + (size_t)v * D;
-            // Orbit member mm of the centred pixel (ip, jp) is (ip, jp), (-jp, ip),
-            // (-ip, -jp), (jp, -ip), so its projective denominator and numerator are
-            // signed combinations of four products shared by the members.
-            const T ip0 = (T)i - cx, jp0 = (T)j - cy;
-            const T pa = w.di * ip0 + w.dj * jp0, pb = w.dj * ip0 - w.di * jp0;
-            const T na = w.ni * ip0 + w.nj * jp0, nb = w.nj * ip0 - w.ni * jp0;
+            if (!redo) {
+                // Record `lane` of a group: bin lane % kBpWin of slot lane / kBpWin; off the
+                // detector the zero record that ends each row of the ray table.
+                BpRay<T> pr;
+                T pv[W];
+                const int ssl = lane / kBpWin, sk = lane % kBpWin;
+                auto stage = [&](int t, int g) {
+                    const unsigned b =
+                        (unsigned)(bp_slot_window(slots[t * SPV + g * kBpSlots + ssl].info) + sk);
+                    const unsigned br = min(b, (unsigned)D), bs = min(b, (unsigned)(D - 1));
+                    if constexpr (SYM == 4) {
+                        const int v = view_of(t0 + t, 0);
+                        pr = ray_at(v, br);
+                        values_at(v, bs, pv);
+                    } else {
+                        // Two views: the second one's row is one stride further (the last
+                        // row is its own partner when the views run out; its slot has C = 0).
+                        const int v = view_of(t0 + t, 0);
+                        const unsigned more = v + 1 < Vb ? (unsigned)ssl : 0u;
+                        pr = ray_at(v, br + more * (unsigned)(D + 1));
+                        values_at(v, bs + more * (unsigned)D, pv);
+                    }
+                };
+                stage(0, 0);
+#pragma unroll 1
+                for (int t = 0; t < nt; ++t) {
 #pragma unroll
-            for (int mm = 0; mm < SYM; ++mm) {
+                    for (int g = 0; g < GPV; ++g) {
+                        BpSlot e[kBpSlots];
+#pragma unroll
+                        for (int sl = 0; sl < kBpSlots; ++sl)
+                            e[sl] = slots[t * SPV + g * kBpSlots + sl];
+                        store(pr, pv);
+                        // LDS operations of one wave complete in order; the barrier only
+                        // keeps the compiler from moving the reads above the writes.
+                        __builtin_amdgcn_wave_barrier();
+                        if (g + 1 < GPV) stage(t, g + 1);
+                        else if (t + 1 < nt) stage(t + 1, 0);
+#pragma unroll
+                        for (int sl = 0; sl < kBpSlots; ++sl) {
+                            const int mm = SYM == 4 ? g * kBpSlots + sl : 0;
+                            int im, jm;
+                            rot(mm, n, i, j, im, jm);
+                            const T fi = (T)im, fj = (T)jm;
+                            const int C = __builtin_amdgcn_readfirstlane(e[sl].info) & 255;
+                            const int o = sl * kBpWin + bp_slot_start(e[sl], oi, oj);
+                            auto take = [&](int k) {
+                                BpRay<T> r;
+                                T s[W];
+                                fetch(o + k, r, s);
+                                const T wt = weight(r, fi, fj);
+#pragma unroll
+                                for (int kp = 0; kp < SYM; ++kp)
+#pragma unroll
+                                    for (int c = 0; c < CH; ++c) {
+                                        A& x = acc[(mm + kp) % SYM][c];
+                                        x = fma((A)wt, (A)s[kp * CH + c], x);
+                                    }
+                            };
+                            if ((unsigned)(C - 1) < (unsigned)(kBpLong - 1)) {
+                                take(0);
+                                take(1);
+#pragma unroll 1
+                                for (int k = 2; k < C; ++k) take(k);
+                            }
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            }
+#pragma unroll 1
+            while (left) {  // slots with long windows, and direct ones
+                const int s0 = __ffsll((long long)left) - 1;
+                left &= left - 1;
+                const int v = view_of(t0 + s0 / SPV, s0 % SPV), mm = SYM == 4 ? s0 % SPV : 0;
                 int im, jm;
                 rot(mm, n, i, j, im, jm);
                 const T fi = (T)im, fj = (T)jm;
-                const T dq = (mm & 1) ? pb : pa, nq = (mm & 1) ? nb : na;
-                // The denominator is positive for every image pixel (the plan keeps a
-                // fan's source outside the image), so |d beta / d i| and
-                // |d beta / d j| share the factor inv.
-                const T inv = fast_rcp<T>(mm & 2 ? w.d0 - dq : w.d0 + dq);
-                const T bq = (mm & 2 ? -nq : nq) * inv;
-                const T h = fma(fmax(fabs(w.nj - bq * w.dj), fabs(w.ni - bq * w.di)), inv, m);
-                auto add = [&](const BpRay<T>& r, const T* s) {
-                    const T d = fma(r.ci, fi, fma(r.cj, fj, r.phi0));
-                    const T wt = fmax(T(0), fma(-r.step, fabs(d), r.step));
+                A sum[W];
 #pragma unroll
-                    for (int kp = 0; kp < SYM; ++kp)
+                for (int c = 0; c < W; ++c) sum[c] = A(0);
+                auto add = [&](T wt, const T (&s)[W]) {
 #pragma unroll
-                        for (int c = 0; c < CH; ++c)
-                            acc[(mm + kp) % SYM][c] =
-                                fma((A)wt, (A)s[kp * CH + c], acc[(mm + kp) % SYM][c]);
+                    for (int c = 0; c < W; ++c) sum[c] = fma((A)wt, (A)s[c], sum[c]);
                 };
-                // Candidates in the window come from LDS, in window coordinates (bins
-                // of the window past the detector's ends hold zero records and add
-                // nothing).  The rest (a steep footprint near the source, rare) are
-                // loaded directly, after them, when some lane of the wave has any.
-                const T x = bq + (w.boff - (T)L[mm]);
-                const int ilo = min((int)ceil(fmax(x - h, T(0))), WIN);
-                const int ihi = (int)floor(fmin(x + h, T(WIN - 1)));
-                const Staged<T, CH, SYM>* sw = &s_win[wave][mm * kWideStride];
-                const Staged<T, CH, SYM>* c = sw + ilo;
-#pragma unroll
-                for (int t = 0; t < kBpFixed; ++t) add(c[t].r, c[t].s);
-                for (c += kBpFixed; c <= sw + ihi; ++c) add(c->r, c->s);
-                if (__any(x - h < T(0) || x + h > T(WIN - 1))) {
+                const BpSlot e = slots[s0];
+                const int info = __builtin_amdgcn_readfirstlane(e.info);
+                if (info & kBpLong) {  // one slot staged by all lanes
+                    const unsigned b = (unsigned)(bp_slot_window(info) + lane);
+                    T s[W];
+                    BpRay<T> r = ray_at(v, min(b, (unsigned)D));
+                    values_at(v, min(b, (unsigned)(D - 1)), s);
+                    store(r, s);
+                    __builtin_amdgcn_wave_barrier();
+                    const int o = bp_slot_start(e, oi, oj), C = info & (kBpLong - 1);
+                    for (int k = 0; k < C; ++k) {
+                        fetch(o + k, r, s);
+                        add(weight(r, fi, fj), s);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                } else {  // candidate by candidate from global memory
+                    const ViewParam<T> w = a.views[v];
+                    const T ip = fi - T(0.5) * (T)(n - 1), jp = fj - T(0.5) * (T)(a.ny - 1);
+                    const T inv = fast_rcp<T>(w.d0 + w.di * ip + w.dj * jp);
+                    const T bq = (w.ni * ip + w.nj * jp) * inv;
+                    // A point one pixel away along an axis is off by |g| / (1 - |e|) at most
+                    // (|e| < 1/2: the source is two pixels outside the image's circle).
+                    const T h =
+                        fmax(fabs((w.nj - bq * w.dj) * inv) / (T(1) - fabs(w.dj * inv)),
+                             fabs((w.ni - bq * w.di) * inv) / (T(1) - fabs(w.di * inv))) +
+                        T(0.02);
                     const T bc = bq + w.boff;
-                    const int lo = (int)ceil(fmax(bc - h, T(0)));
-                    const int hi = (int)floor(fmin(bc + h, T(D - 1)));
-                    const int below = min(hi, L[mm] - 1), above = max(lo, L[mm] + WIN);
-                    for (int b = lo; b <= below; ++b) add(rv[b], sq[b].v);
-                    for (int b = above; b <= hi; ++b) add(rv[b], sq[b].v);
+                    const int lo = (int)ceil(fmin(fmax(bc - h, T(0)), (T)D));
+                    const int hi = (int)floor(fmax(fmin(bc + h, (T)(D - 1)), T(-1)));
+                    for (int b = lo; b <= hi; ++b) {
+                        T s[W];
+                        values_at(v, (unsigned)b, s);
+                        add(weight(ray_at(v, (unsigned)b), fi, fj), s);
+                    }
                 }
+#pragma unroll
+                for (int m = 0; m < SYM; ++m)
+                    if (m == mm)
+#pragma unroll
+                        for (int kp = 0; kp < SYM; ++kp)
+#pragma unroll
+                            for (int c = 0; c < CH; ++c)
+                                acc[(m + kp) % SYM][c] += sum[kp * CH + c];
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        bool finite = true;
+#pragma unroll
+        for (int k = 0; k < SYM; ++k)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) finite = finite && isfinite(acc[k][c]);
+        if (redo || !__any(!finite)) break;
+        redo = 1;
+#pragma unroll
+        for (int k = 0; k < SYM; ++k)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[k][c] = A(0);
     }
 }
-
 
 // R^T (+ epilogue).  A workgroup owns an 8x8 block of pixel orbits (the block
 // lies in the first quadrant when SYM = 4) and has VS waves, each summing a
-// disjoint subset of the base views; wave 0 adds the others' sums in order.  A: the
-// type the sums are kept in (T, or double for an FP32 plan's sums in double precision:
-// each product of two FP32 values is exact in double, so only the sums round); the
-// finished values are rounded to T once.
-template <typename T, int CH, int SYM, bool QUAD, int EPI, int VS, bool BATCH, typename A = T>
-__global__ __launch_bounds__(64 * VS) void k_backproject(const BpArgs<T>* __restrict__ dev,
-                                                         BpArgs<T> one, unsigned nslices) {
-    // The ADMM epilogues (q, dual) run one orbit member per wave; the plain transpose
-    // keeps the reduction into wave 0.
-    constexpr bool kFinish = EPI == EPI_Q || EPI == EPI_DUAL;
-    constexpr bool kWide = QUAD && SYM == 4;
-    // The wide staging windows, one row per wave.  For the ADMM epilogues each wave
-    // then stores its view sums over its own (by then idle) row.
-    using St = Staged<T, CH, SYM>;
-    __shared__ St s_win[kWide ? VS : 1][kWide ? kWideStride * SYM : 1];
-    constexpr int kRed = kFinish ? (kWide ? 1 : VS) : (VS > 1 ? VS - 1 : 1);
-    __shared__ A red_own[kRed][64][SYM * CH];
-    static_assert(!kWide || sizeof(A) * 64 * SYM * CH <= sizeof(St) * kWideStride * SYM,
-                  "a wave's view sums fit in its staging row");
-    auto red = [&](int w) -> A(*)[SYM * CH] {
-        if constexpr (kFinish && kWide) return reinterpret_cast<A(*)[SYM * CH]>(&s_win[w][0]);
-        else return red_own[w];
+// disjoint subset of the base views.  Sinograms are records of the SYM views of a base
+// ray ([Vb][D][SYM][CH]).  A: the type the sums are kept in (T, or double for an FP32
+// plan's sums in double precision: each product of two FP32 values is exact in double, so
+// only the sums round); the finished values are rounded to T once.
+//
+// Waves per SIMD that the registers are held to (the second launch bound).  The staged gather
+// waits on LDS, so it wants as many waves as its registers allow; what is spilled for them is
+// the batch's set-up and the epilogue, outside the candidate loops.
+template <typename T, typename A, int W>
+constexpr int bp_min_waves() {
+    if (sizeof(T) == 8) return W <= 2 ? 6 : W <= 4 ? 5 : W <= 8 ? 3 : 2;
+    if (sizeof(A) == 8) return W <= 2 ? 8 : 5;
+    return W <= 8 ? 8 : 5;
+}
+
+template <typename T, int CH, int SYM, int EPI, int VS, bool BATCH, typename A = T>
+__global__ __launch_bounds__(64 * VS, (bp_min_waves<T, A, CH * SYM>())) void k_backproject(
+    const BpArgs<T>* __restrict__ dev, BpArgs<T> one, unsigned nslices) {
+    constexpr int W = SYM * CH;
+    // Each wave's staging window; once its view sums are done it stores them over it.
+    using Win = BpWindow<T, W>;
+    union alignas(16) Row {
+        Win win;
+        A sum[64][W];
+        __device__ Row() {}
     };
-    // The orbit block (bx, by) of this workgroup: its 2-D grid position for one slice;
-    // in a batch, a 1-D grid that gives each XCD an equal contiguous share of the
-    // slices' blocks (one.gx, one.gy: the group's block grid, the same for all its
-    // slices).
-    int bx, by;
-    unsigned slice = 0;
+    __shared__ Row s_row[VS];
+    __shared__ BpSlot s_slot[VS][kBpBatch];
+    // The orbit block (bx, by) of this workgroup: by launch position in the plan's order; in
+    // a batch each XCD takes an equal contiguous share of the slices' positions (one.gx,
+    // one.gy: the group's block grid, the same for all its slices).
+    unsigned slice = 0, pos = blockIdx.x;
     if constexpr (BATCH) {
-        unsigned tile;
-        if (!xcd_slice_tile(blockIdx.x, (unsigned)(one.gx * one.gy), nslices, slice, tile))
-            return;
-        bx = (int)(tile % (unsigned)one.gx);
-        by = (int)(tile / (unsigned)one.gx);
-    } else {
-        bx = (int)blockIdx.x;
-        by = (int)blockIdx.y;
+        if (!xcd_slice_tile(blockIdx.x, (unsigned)(one.gx * one.gy), nslices, slice, pos)) return;
     }
     const BpArgs<T> a = pick_args<BATCH>(dev, one, slice);
-    if (bx >= a.gx || by >= a.gy) return;  // beyond this slice
+    const int tile = a.order[pos], bx = tile % a.gx, by = tile / a.gx;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int i = bx * 8 + (lane & 7);
-    const int j = by * 8 + (lane >> 3);
-    const int dom_x = SYM == 4 ? a.nx / 2 : a.nx, dom_y = SYM == 4 ? a.ny / 2 : a.ny;
-    const bool inside = i < dom_x && j < dom_y;
     A acc[SYM][CH];
 #pragma unroll
     for (int k = 0; k < SYM; ++k)
 #pragma unroll
         for (int c = 0; c < CH; ++c) acc[k][c] = A(0);
-    if constexpr (kWide)
-        gather_orbit_staged_wide<T, A, CH, SYM, VS>(a, wave, lane, i, j, bx, by, inside, acc, s_win);
-    else if constexpr (QUAD)
-        gather_orbit_staged<T, A, CH, SYM, VS>(a, wave, lane, i, j, bx, by, inside, acc);
-    else if (inside)
-        gather_orbit<T, A, CH, SYM, VS>(a, wave, i, j, acc);
-    if constexpr (kFinish) {
-        // Every wave's view sums go to LDS; wave w then finishes orbit members w, w + VS,
-        // ...: it adds the waves' sums in wave order, runs the epilogue of its member
-        // and reduces its partials over its lanes; thread 0 adds the members' partials
-        // in member order.
-        __shared__ double wpart[SYM][2];
-        {
-            A(*mine)[SYM * CH] = red(wave);
+    gather_windows<T, A, CH, SYM, VS>(a, wave, lane, bx, by, s_row[wave].win, s_slot[wave],
+                                            acc);
+    // Every wave's view sums go to LDS; wave w then finishes orbit members w, w + VS, ...:
+    // it adds the waves' sums in wave order and stores the member's pixels or runs its
+    // epilogue, whose partials it reduces over its lanes; thread 0 adds the members'
+    // partials in member order.
 #pragma unroll
-            for (int k = 0; k < SYM; ++k)
+    for (int k = 0; k < SYM; ++k)
 #pragma unroll
-                for (int c = 0; c < CH; ++c) mine[lane][k * CH + c] = acc[k][c];
-        }
-        __syncthreads();
-        for (int k = wave; k < SYM; k += VS) {
-            A sum[2] = {A(0), A(0)};
-            for (int w = 0; w < VS; ++w)
+        for (int c = 0; c < CH; ++c) s_row[wave].sum[lane][k * CH + c] = acc[k][c];
+    __shared__ double wpart[SYM][2];
+    __syncthreads();
+    const int i = bx * 8 + (lane & 7), j = by * 8 + (lane >> 3);
+    const int dom_x = SYM == 4 ? a.nx / 2 : a.nx, dom_y = SYM == 4 ? a.ny / 2 : a.ny;
+    const bool inside = i < dom_x && j < dom_y;
+    for (int k = wave; k < SYM; k += VS) {
+        A sum[CH];
 #pragma unroll
-                for (int c = 0; c < 2; ++c) sum[c] += red(w)[lane][k * CH + (CH > 1 ? c : 0)];
-            T res[2] = {(T)sum[0], (T)sum[1]};
-            double part[2] = {0.0, 0.0};
+        for (int c = 0; c < CH; ++c) sum[c] = A(0);
+        for (int w = 0; w < VS; ++w)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) sum[c] += s_row[w].sum[lane][k * CH + c];
+        int io, jo;
+        rot(k, a.nx, i, j, io, jo);
+        if constexpr (EPI == EPI_NONE) {
             if (inside) {
-                int io, jo;
-                rot(k, a.nx, i, j, io, jo);
-                epilogue<T, EPI>(a, io, jo, res, part);
+                vec<T, CH> o;
+#pragma unroll
+                for (int c = 0; c < CH; ++c) o.v[c] = (T)sum[c];
+                reinterpret_cast<vec<T, CH>*>(a.out)[(size_t)jo * a.nx + io] = o;
             }
+        } else {
+            T res[2] = {(T)sum[0], (T)sum[CH > 1 ? 1 : 0]};
+            double part[2] = {0.0, 0.0};
+            if (inside) epilogue<T, EPI>(a, io, jo, res, part);
 #pragma unroll
             for (int c = 0; c < 2; ++c)
                 for (int off = 32; off > 0; off >>= 1) part[c] += __shfl_down(part[c], off, 64);
@@ -833,6 +784,8 @@ __global__ __launch_bounds__(64 * VS) void k_backproject(const BpArgs<T>* __rest
                 wpart[k][1] = part[1];
             }
         }
+    }
+    if constexpr (EPI != EPI_NONE) {
         __syncthreads();
         if (threadIdx.x == 0) {
             double o0 = 0.0, o1 = 0.0;
@@ -844,57 +797,12 @@ __global__ __launch_bounds__(64 * VS) void k_backproject(const BpArgs<T>* __rest
             o[0] = o0;
             o[1] = o1;
         }
-        return;
-    } else {
-        if constexpr (VS > 1) {
-            if (wave > 0)
-#pragma unroll
-                for (int k = 0; k < SYM; ++k)
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) red_own[wave - 1][lane][k * CH + c] = acc[k][c];
-            __syncthreads();
-            if (wave == 0)
-                for (int w = 0; w < VS - 1; ++w)
-#pragma unroll
-                    for (int k = 0; k < SYM; ++k)
-#pragma unroll
-                        for (int c = 0; c < CH; ++c) acc[k][c] += red_own[w][lane][k * CH + c];
-        }
-        if (wave != 0) return;
-        double part[2] = {0.0, 0.0};
-        if (inside) {
-#pragma unroll
-            for (int k = 0; k < SYM; ++k) {
-                int io, jo;
-                rot(k, a.nx, i, j, io, jo);
-                if constexpr (EPI == EPI_NONE) {
-                    vec<T, CH> o;
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) o.v[c] = (T)acc[k][c];
-                    reinterpret_cast<vec<T, CH>*>(a.out)[(size_t)jo * a.nx + io] = o;
-                } else {
-                    T res[2] = {(T)acc[k][0], (T)acc[k][CH > 1 ? 1 : 0]};
-                    epilogue<T, EPI>(a, io, jo, res, part);
-                }
-            }
-        }
-        if constexpr (EPI != EPI_NONE) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-                for (int off = 32; off > 0; off >>= 1) part[c] += __shfl_down(part[c], off, 64);
-            if (lane == 0) {
-                double* o = a.partials + (size_t)(by * a.gx + bx) * kPartialSlots;
-                o[0] = part[0];
-                o[1] = part[1];
-            }
-        }
     }
 }
 
-// Waves per workgroup of the plain transposed projector and projector; the ADMM
-// kernels take theirs from the plan (2, 4 or 8; see dect_plan_tune).  8 projector
+// Waves per workgroup of the plain projector; the other kernels take theirs from the plan
+// (2, 4 or 8; see dect_plan_tune).  8 projector
 // waves took the LM1 x CG1 iteration at 512^2 from 1.01 to 0.96 ms against 4.
-constexpr int kViewSplit = 4;
 constexpr int kLineSplit = 8;
 
 template <typename T, int CH, int SYM, bool QUAD, bool BATCH, int KS>
@@ -932,70 +840,83 @@ hipError_t project_t(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone,
 }
 
 // A standard [V][D][CH] sinogram as quad records [Vb][D][4][CH] (view v + k Vb is
-// rotation k of base view v), the layout the staged transpose reads.
+// rotation k of base view v), the layout the transpose of a quarter-turn symmetric plan
+// reads: one record per thread, the four views' rows read and the records written along b.
 template <typename T, int CH>
 __global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino, int Vb, int D,
                                                       T* __restrict__ quad) {
-    const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;  // (vb, b, k)
-    if (r >= (long)Vb * D * 4) return;
-    const int k = (int)(r & 3);
-    const long vb_b = r >> 2;
-    const int vb = (int)(vb_b / D), b = (int)(vb_b % D);
-    const T* src = sino + ((size_t)(vb + k * Vb) * D + b) * CH;
+    const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;  // (vb, b)
+    const long rows = (long)Vb * D;
+    if (r >= rows) return;
+    vec<T, 4 * CH> o;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) quad[r * CH + c] = src[c];
+    for (int k = 0; k < 4; ++k) {
+        const vec<T, CH> t = reinterpret_cast<const vec<T, CH>*>(sino)[r + k * rows];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) o.v[k * CH + c] = t.v[c];
+    }
+    reinterpret_cast<vec<T, 4 * CH>*>(quad)[r] = o;
 }
 
-// R^T of one or two channels on a quarter-turn symmetric plan: the sinogram is
-// reordered into quad records in the plan's scratch and gathered by the staged
-// transpose with `waves` waves per workgroup.
-template <typename T, int CH, int VS>
-hipError_t bp_quad_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
-    const long recs = (long)one.Vb * one.D * 4;
-    hipLaunchKernelGGL((k_quad_records<T, CH>), dim3((unsigned)((recs + 255) / 256)), dim3(256),
-                       0, s, one.sino, one.Vb, one.D, quad);
+// Plain R^T of a standard [V][D][CH] sinogram with `waves` waves per workgroup; on a
+// quarter-turn symmetric plan it is first reordered into quad records (plan scratch):
+// staging straight from the four views' rows measured 146 us against 105 us + 4 us.
+template <typename T, int CH, int SYM, int VS>
+hipError_t bp_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
     BpArgs<T> a = one;
-    a.sino = quad;
-    hipLaunchKernelGGL((k_backproject<T, CH, 4, true, EPI_NONE, VS, false>), dim3(a.gx, a.gy),
+    if constexpr (SYM == 4) {
+        const long recs = (long)one.Vb * one.D;
+        hipLaunchKernelGGL((k_quad_records<T, CH>), dim3((unsigned)((recs + 255) / 256)), dim3(256),
+                           0, s, one.sino, one.Vb, one.D, quad);
+        a.sino = quad;
+    }
+    hipLaunchKernelGGL((k_backproject<T, CH, SYM, EPI_NONE, VS, false>), dim3(one.gx * one.gy),
                        dim3(64 * VS), 0, s, nullptr, a, 1u);
     return hipGetLastError();
 }
 
-template <typename T, int CH>
-hipError_t bp_quad_plain_w(int waves, const BpArgs<T>& one, T* quad, hipStream_t s) {
-    switch (waves) {
-        case 2: return bp_quad_plain<T, CH, 2>(one, quad, s);
-        case 4: return bp_quad_plain<T, CH, 4>(one, quad, s);
-        case 8: return bp_quad_plain<T, CH, 8>(one, quad, s);
-    }
-    return hipErrorInvalidValue;
+// Waves per workgroup of a transpose launch: the plan's choice, doubled (to at most 16) while
+// the slice's blocks would leave a compute unit fewer than 64 waves: at 256^2 (256 blocks)
+// 4, 8 and 16 waves took 58, 38 and 31 us, at 512^2 8 and 16 waves the same 107 us.  It hangs on the slice's blocks alone, so a batch
+// sums as its slices do.  Wide double-precision records keep to 8 (registers).
+template <typename T, int W>
+int bp_waves_for(int waves, int blocks) {
+    const int most = sizeof(T) == 8 && W > 4 ? 8 : 16;
+    while (waves < most && (long)blocks * waves < 256l * 64) waves *= 2;
+    return waves;
 }
 
 template <typename T, int CH, int SYM>
-hipError_t bp_plain(const BpArgs<T>& one, hipStream_t s) {
-    hipLaunchKernelGGL((k_backproject<T, CH, SYM, false, EPI_NONE, kViewSplit, false>),
-                       dim3(one.gx, one.gy), dim3(64 * kViewSplit), 0, s, nullptr, one, 1u);
-    return hipGetLastError();
+hipError_t bp_plain_w(int waves, const BpArgs<T>& one, T* quad, hipStream_t s) {
+    switch (bp_waves_for<T, CH * SYM>(waves, one.gx * one.gy)) {
+        case 2: return bp_plain<T, CH, SYM, 2>(one, quad, s);
+        case 4: return bp_plain<T, CH, SYM, 4>(one, quad, s);
+        case 8: return bp_plain<T, CH, SYM, 8>(one, quad, s);
+        case 16:
+            if constexpr (sizeof(T) == 4 || CH * SYM <= 4)
+                return bp_plain<T, CH, SYM, 16>(one, quad, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 // The ADMM's own sinograms are two-channel quad records.
 template <typename T, int SYM, bool BATCH, int VS, typename A>
 hipError_t bp_admm_t(int epi, const BpArgs<T>* dev, const BpArgs<T>& one, int n, int gx, int gy,
                      hipStream_t s) {
-    // One slice: a (gx, gy) grid.  A batch: each XCD an equal contiguous share of the
-    // slices' blocks; the kernel takes the block grid from `one`, the same for every
-    // slice of the group.
+    // One slice: a workgroup per block.  A batch: each XCD an equal contiguous share of the
+    // slices' blocks; the kernel takes the block grid from `one`, the same for every slice
+    // of the group.
     if (gx != one.gx || gy != one.gy) return hipErrorInvalidValue;
-    const dim3 g = BATCH ? dim3(xcd_slice_blocks((unsigned)(gx * gy), (unsigned)n)) : dim3(gx, gy);
+    const dim3 g(BATCH ? xcd_slice_blocks((unsigned)(gx * gy), (unsigned)n) : (unsigned)(gx * gy));
     const dim3 blk(64 * VS);
     const unsigned nsl = (unsigned)n;
     switch (epi) {
         case EPI_Q:
-            hipLaunchKernelGGL((k_backproject<T, 2, SYM, true, EPI_Q, VS, BATCH, A>), g, blk, 0, s,
+            hipLaunchKernelGGL((k_backproject<T, 2, SYM, EPI_Q, VS, BATCH, A>), g, blk, 0, s,
                                dev, one, nsl);
             break;
         case EPI_DUAL:
-            hipLaunchKernelGGL((k_backproject<T, 2, SYM, true, EPI_DUAL, VS, BATCH, A>), g, blk, 0,
+            hipLaunchKernelGGL((k_backproject<T, 2, SYM, EPI_DUAL, VS, BATCH, A>), g, blk, 0,
                                s, dev, one, nsl);
             break;
         default:
@@ -1007,10 +928,13 @@ hipError_t bp_admm_t(int epi, const BpArgs<T>* dev, const BpArgs<T>& one, int n,
 template <typename T, int SYM, bool BATCH, typename A>
 hipError_t bp_admm_w(int waves, int epi, const BpArgs<T>* dev, const BpArgs<T>& one, int n, int gx,
                      int gy, hipStream_t s) {
-    switch (waves) {
+    switch (bp_waves_for<T, 2 * SYM>(waves, gx * gy)) {
         case 2: return bp_admm_t<T, SYM, BATCH, 2, A>(epi, dev, one, n, gx, gy, s);
         case 4: return bp_admm_t<T, SYM, BATCH, 4, A>(epi, dev, one, n, gx, gy, s);
         case 8: return bp_admm_t<T, SYM, BATCH, 8, A>(epi, dev, one, n, gx, gy, s);
+        case 16:
+            if constexpr (sizeof(T) == 4 || SYM == 1)
+                return bp_admm_t<T, SYM, BATCH, 16, A>(epi, dev, one, n, gx, gy, s);
     }
     return hipErrorInvalidValue;
 }
@@ -1052,10 +976,10 @@ void fill_bp_plan(const dect_plan* p, BpArgs<T>& a) {
     a.V = p->V;
     a.Vb = p->Vb;
     a.D = p->D;
-    a.margin = p->margin;
     const int dx = p->sym == 4 ? p->nx / 2 : p->nx, dy = p->sym == 4 ? p->ny / 2 : p->ny;
     a.gx = (dx + 7) / 8;
     a.gy = (dy + 7) / 8;
+    a.order = p->bp_order;
 }
 
 // R into the standard sinogram layout, with the two orbit images of the image in O and
@@ -1124,15 +1048,15 @@ hipError_t launch_backproject(const dect_plan* p, int ch, const BpArgs<T>& a0, h
     if (p->sym == 4) {
         T* quad = static_cast<T*>(p->scratch_sq);
         switch (ch) {
-            case 1: return bp_quad_plain_w<T, 1>(p->bp_waves, a, quad, s);
-            case 2: return bp_quad_plain_w<T, 2>(p->bp_waves, a, quad, s);
-            case 4: return bp_plain<T, 4, 4>(a, s);
+            case 1: return bp_plain_w<T, 1, 4>(p->bp_waves, a, quad, s);
+            case 2: return bp_plain_w<T, 2, 4>(p->bp_waves, a, quad, s);
+            case 4: return bp_plain_w<T, 4, 4>(p->bp_waves, a, quad, s);
         }
     } else {
         switch (ch) {
-            case 1: return bp_plain<T, 1, 1>(a, s);
-            case 2: return bp_plain<T, 2, 1>(a, s);
-            case 4: return bp_plain<T, 4, 1>(a, s);
+            case 1: return bp_plain_w<T, 1, 1>(p->bp_waves, a, nullptr, s);
+            case 2: return bp_plain_w<T, 2, 1>(p->bp_waves, a, nullptr, s);
+            case 4: return bp_plain_w<T, 4, 1>(p->bp_waves, a, nullptr, s);
         }
     }
     return hipErrorInvalidValue;
