@@ -354,7 +354,8 @@ dect_status dect_lmcg_iterate(const dect_plan* plan, const void* m_h, const void
  *  - proj_waves: waves of a projector workgroup, splitting the lines its rays cross
  *    (2, 4 or 8);
  *  - proj_views: base views whose rays share a projector wave (1, 2, 4 or 8; the wave
- *    takes 64 / proj_views consecutive bins of each);
+ *    takes 64 / proj_views consecutive bins of each; on large grids a lane takes two rays
+ *    and the wave 32 / proj_views bins of 4 proj_views views);
  *  - proj_chunk: bin groups an XCD takes per turn of the workgroup order (1 to 16).
  * Defaults 4, 8, 2, 1.  Every shape computes the same sums; only the order in which a
  * workgroup's partial sums are added changes.  Batches share launches only between

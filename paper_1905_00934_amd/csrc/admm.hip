@@ -253,9 +253,11 @@ SliceJob<T> make_job(const dect_plan* p, const void* mh, const void* ml, const v
     J.pj_chunk = p->pj_chunk;
     J.pj_gx = proj_grid_x(p->D, p->pj_views);
     J.pj_gy = proj_grid_y(p->Vb, p->pj_views);
+    J.pj_rays = proj_rays((int)sizeof(T) * 2 * p->sym, p->Vb, p->D, p->pj_views, p->pj_waves);
     J.orb = OrbitArgs<T>{pp, pO, pOT, p->nx, p->ny};
     J.prj = ProjArgs<T>{static_cast<const RayParam<T>*>(p->rays), pO, pOT, Rp, p->nx, p->ny,
-                        p->Vb, p->D, p->pj_views, p->pj_chunk};
+                        p->Vb, p->D, p->pj_views, {p->pj_order[0], p->pj_order[1]},
+                        {p->pj_blocks[0], p->pj_blocks[1]}, 0};
     // Right-hand side of Eq. (12) and the initial CG residual.
     BpArgs<T> b{};
     fill_bp_plan<T>(p, b);
@@ -391,8 +393,8 @@ hipError_t iteration_t(const SliceJob<T>& J, const JobArrays<T>* dev, int nsl,
     if (J.precond) DECT_TRY(launch_precond<T>(dev ? dev->pre0 : nullptr, J.pre0, nsl, s));
     for (int c = 0; c < n; ++c) {
         DECT_TRY(launch_project_pair<T>(J.sym, J.pj_waves, dev ? dev->orb : nullptr, J.orb,
-                                        dev ? dev->prj : nullptr, J.prj, nsl, J.N, J.pj_gx,
-                                        J.pj_gy, s, !(fused && c == 0)));
+                                        dev ? dev->prj : nullptr, J.prj, nsl, J.N, s,
+                                        !(fused && c == 0)));
         DECT_TRY(launch_backproject_admm<T>(J.sym, J.bp_waves, EPI_Q, dev ? dev->q : nullptr, J.q,
                                             nsl, J.bp_gx, J.bp_gy, s, J.rt_sums64 != 0));
         DECT_TRY(reduce(RED_ALPHA));

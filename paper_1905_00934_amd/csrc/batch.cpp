@@ -5,6 +5,7 @@
 // Slices are independent problems (one per detector row or table position); a
 // slice's kernels read only its own argument block, so its result does not
 // depend on which other slices share the launches.
+#include <algorithm>
 #include <cstring>
 #include <memory>
 
@@ -21,6 +22,7 @@ template <typename T>
 bool same_shape(const SliceJob<T>& a, const SliceJob<T>& b) {
     return a.N == b.N && a.M == b.M && a.sym == b.sym && a.bp_gx == b.bp_gx &&
            a.bp_gy == b.bp_gy && a.pj_gx == b.pj_gx && a.pj_gy == b.pj_gy &&
+           a.pj_rays == b.pj_rays &&
            a.prj.nx == b.prj.nx && a.prj.ny == b.prj.ny && a.cg_iters == b.cg_iters &&
            a.rho_mode == b.rho_mode && a.bp_waves == b.bp_waves && a.pj_waves == b.pj_waves &&
            a.pj_views == b.pj_views && a.pj_chunk == b.pj_chunk &&
@@ -79,6 +81,8 @@ hipError_t Runner<T>::set(const std::vector<SliceJob<T>>& jobs) {
             into = &groups_.back();
         }
         into->jobs.push_back(J);
+        int& grid = into->jobs[0].prj.grid;
+        grid = std::max(grid, J.prj.blocks[J.pj_rays - 1]);
     }
     size_t total = 0;
     std::vector<ArrayOffsets<T>> offs;

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "dect.h"
+#include "projorder.h"
 
 namespace dect {
 
@@ -64,11 +65,9 @@ struct alignas(sizeof(T) * 4) BpRay {
 // bins) of the ray through the point with centred pixel coordinates (i', j') is
 //   beta = (ni i' + nj j') / (d0 + di i' + dj j') + boff
 // (fan beam: central projection from the source; parallel: d0 = 1, di = dj = 0).
-// Bins [xb0, xb1) of the view are x-stepped, [yb0, yb1) y-stepped.
 template <typename T>
 struct ViewParam {
     T ni, nj, d0, di, dj, boff;
-    int xb0, xb1, yb0, yb1;
 };
 
 // Energy-bin tables of one spectrum in base-2 units: the normalised weight as
@@ -100,6 +99,17 @@ struct dect_plan {
     // Projector lane layout (base views per wave) and XCD chunk (bin groups per XCD
     // turn), also set by dect_plan_tune.
     int pj_views = 2, pj_chunk = 1;
+    std::vector<dect::ViewSplit> splits;  // per base view, the bins of each ray axis
+    // Workgroup lists of the projector for the launch shapes used so far, kept (never
+    // rewritten) until the plan goes, by rays per lane - 1 (proj_order_for).
+    struct ProjOrder {
+        int views, chunk;
+        int* order[2];
+        int blocks[2];
+    };
+    std::vector<ProjOrder> pj_orders;
+    const int* pj_order[2] = {nullptr, nullptr};  // of the current shape
+    int pj_blocks[2] = {0, 0};
     // device tables
     void* rays = nullptr;   // RayParam<T>[Vb * D]
     void* views = nullptr;  // ViewParam<T>[Vb]
@@ -159,6 +169,11 @@ namespace dect {
 
 // Workgroups of the transposed projector (8x8 pixel orbits each).
 int bp_blocks(const dect_plan* p);
+
+// The projector's workgroup lists for a lane layout and chunk (device tables) and their
+// lengths, built on first use.
+dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&order)[2],
+                           int (&blocks)[2]);
 
 // Column i and row j of pixel pix of an image nx wide; images hold fewer than 2^30
 // pixels, so the division is unsigned 32-bit.

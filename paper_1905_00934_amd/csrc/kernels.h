@@ -82,7 +82,10 @@ struct ProjArgs {
     const T* OT;
     T* sino;
     int nx, ny, Vb, D;
-    int views, chunk;  // base views per wave (a power of two) and bin groups per XCD turn
+    int views;            // base views per wave (a power of two)
+    const int* order[2];  // the workgroup lists (tile and axis), by rays per lane - 1
+    int blocks[2];        // their lengths
+    int grid;             // workgroups of the launch if more: a batch's longest list
 };
 
 // Fixed-order reductions of block partials and the scalar updates (one block per
@@ -108,10 +111,9 @@ struct RedArgs {
 
 template <typename T>
 struct BpArgs {
-    const RayParam<T>* rays;
     const BpRay<T>* brays;
     const ViewParam<T>* views;
-    int nx, ny, V, Vb, D;
+    int nx, ny, Vb, D;
     int gx, gy;   // this slice's grid of 8x8 orbit blocks
     const int* order;  // [gx gy]: the block of each launch position (bp_block_order)
     const T* sino;
@@ -279,15 +281,14 @@ __device__ inline void partial_sums(const double* __restrict__ b0, int n0, doubl
 template <typename T>
 hipError_t launch_project(const dect_plan* p, const void* img, void* sino, int ch, hipStream_t s);
 // Two-channel projection of the ADMM direction into quad-interleaved records, for
-// one slice (dev == nullptr: `one`) or n slices (dev: device arrays); the grid is
-// (gx, gy) projector blocks of `waves` (2, 4 or 8) waves splitting the lines, and
-// `pixels` orbit-image threads per slice.  orbit = false: the orbit images are
+// one slice (dev == nullptr: `one`) or n slices of its shape (dev: device arrays); `waves`
+// (2, 4 or 8) waves per workgroup split the lines, `pixels` orbit-image threads per slice.  orbit = false: the orbit images are
 // already in place (written by launch_rhs_orbit) and only the projector runs.
 template <typename T>
 hipError_t launch_project_pair(int sym, int waves, const OrbitArgs<T>* odev,
                                const OrbitArgs<T>& oone, const ProjArgs<T>* pdev,
-                               const ProjArgs<T>& pone, int n, long pixels, int gx, int gy,
-                               hipStream_t s, bool orbit = true);
+                               const ProjArgs<T>& pone, int n, long pixels, hipStream_t s,
+                               bool orbit = true);
 // The CG right-hand side (as the right-hand-side kernel: r0 into rhs.out and rhs.out2,
 // partials of |r0|^2 per 256 pixels into rhs.part_img) and, in the same launch, the
 // orbit images of r0 into orb.O and orb.OT, for quarter-turn symmetric square slices
@@ -454,6 +455,7 @@ struct SliceJob {
     int precond;
     long N, M;
     int sym, bp_gx, bp_gy, pj_gx, pj_gy;
+    int pj_rays;             // projector rays per lane
     int bp_waves, pj_waves;  // workgroup shapes of the plan
     int pj_views, pj_chunk;  // projector lane layout and workgroup order of the plan
     int cg_iters, rho_mode;  // launch structure: slices share launches only if these agree

@@ -42,6 +42,22 @@ dect_status upload(const void* host, size_t bytes, void** dev) {
     return DECT_OK;
 }
 
+// The same beside a stream capture of this thread: no call that a capture refuses, no work on
+// the default stream.
+dect_status upload_aside(const void* host, size_t bytes, void** dev) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    DECT_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+    hipStream_t s = nullptr;
+    hipError_t e = hipMalloc(dev, bytes);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipMemcpyAsync(*dev, host, bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (s) (void)hipStreamDestroy(s);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    DECT_HIP(e);
+    return DECT_OK;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <typename T>
@@ -53,8 +69,9 @@ dect_status build_tables(dect_plan* p, const dect_spectra* spec) {
     const double d = g.pixel_cm;
     for (int v = 0; v < V; ++v) {
         int first_kind = -1, switches = 0, split = D;
+        const HostView view = host_view(g, v);
         for (int b = 0; b < D; ++b) {
-            HostRay r = host_ray(g, v, b);
+            HostRay r = host_ray(g, view, b);
             RayParam<T>& q = rays[(size_t)v * D + b];
             q.phi0 = (T)r.phi0;
             q.slope = (T)r.slope;
@@ -73,15 +90,9 @@ dect_status build_tables(dect_plan* p, const dect_spectra* spec) {
                         "view %d: x- and y-stepped rays interleave (%d switches); the fan is "
                         "wider than 90 degrees",
                         v, switches);
+        p->splits.push_back({split, first_kind});
         ViewParam<T>& w = views[v];
-        const int lo0 = 0, hi0 = split, lo1 = split, hi1 = D;
-        if (first_kind == 0) {
-            w.xb0 = lo0; w.xb1 = hi0; w.yb0 = lo1; w.yb1 = hi1;
-        } else {
-            w.yb0 = lo0; w.yb1 = hi0; w.xb0 = lo1; w.xb1 = hi1;
-        }
-        const double t = g.angle0 + (double)v * g.span / (double)g.n_views;
-        const double c = std::cos(t), s = std::sin(t);
+        const double c = view.c, s = view.s;
         const double boff = 0.5 * (D - 1) - g.det_offset;
         if (g.kind == DECT_PARALLEL) {
             w.ni = (T)(d * c / g.det_cm);
@@ -396,6 +407,37 @@ void make_layout(dect_plan* p) {
 
 }  // namespace
 
+// Kept per shape, at most 64 of them.  A shape may be chosen while a stream is captured: the
+// copy then runs on a stream of its own, outside the capture.
+dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&order)[2],
+                           int (&blocks)[2]) {
+    const dect_plan::ProjOrder* hit = nullptr;
+    for (const auto& o : p->pj_orders)
+        if (o.views == views && o.chunk == chunk) hit = &o;
+    if (!hit) {
+        dect_plan::ProjOrder o{views, chunk, {nullptr, nullptr}, {0, 0}};
+        for (int R = 1; R <= 2 && R * views <= 64; ++R) {
+            const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
+                                                         R * views, R * R * views, chunk);
+            const dect_status st = upload_aside(t.data(), t.size() * sizeof(int),
+                                                reinterpret_cast<void**>(&o.order[R - 1]));
+            if (st) {
+                (void)hipFree(o.order[0]);
+                (void)hipFree(o.order[1]);
+                return st;
+            }
+            o.blocks[R - 1] = (int)t.size();
+        }
+        p->pj_orders.push_back(o);
+        hit = &p->pj_orders.back();
+    }
+    for (int r = 0; r < 2; ++r) {
+        order[r] = hit->order[r];
+        blocks[r] = hit->blocks[r];
+    }
+    return DECT_OK;
+}
+
 int bp_blocks(const dect_plan* p) {
     const int dx = p->sym == 4 ? p->nx / 2 : p->nx, dy = p->sym == 4 ? p->ny / 2 : p->ny;
     return ((dx + 7) / 8) * ((dy + 7) / 8);
@@ -472,6 +514,7 @@ dect_status dect_plan_create(const dect_geometry* geom, const dect_spectra* spec
     }
     dect_status st = dtype == DECT_F32 ? build_tables<float>(p, spec) : build_tables<double>(p, spec);
     if (st == DECT_OK) st = build_block_order(p);
+    if (st == DECT_OK) st = proj_order_for(p, p->pj_views, p->pj_chunk, p->pj_order, p->pj_blocks);
     if (st == DECT_OK) st = dtype == DECT_F32 ? build_precond<float>(p) : build_precond<double>(p);
     if (st == DECT_OK) st = dtype == DECT_F32 ? build_fbp<float>(p) : build_fbp<double>(p);
     if (st == DECT_OK && hipMalloc(reinterpret_cast<void**>(&p->scratch_part),
@@ -494,6 +537,10 @@ void dect_plan_destroy(dect_plan* p) {
     (void)hipFree(p->views);
     (void)hipFree(p->bp_rays);
     (void)hipFree(p->bp_order);
+    for (auto& o : p->pj_orders) {
+        (void)hipFree(o.order[0]);
+        (void)hipFree(o.order[1]);
+    }
     (void)hipFree(p->spec);
     (void)hipFree(p->joint);
     (void)hipFree(p->scratch_O);

@@ -30,9 +30,15 @@ struct HostRay {
 // span / n_views; bin centre u_b = (b - (n_det - 1)/2 + det_offset) det_cm; parallel
 // rays p.(cos t, sin t) = u_b, fan rays from the source at src_iso_cm (cos t, sin t) to
 // the bin on the flat detector), in pixel units of the image grid.
-inline HostRay host_ray(const dect_geometry& g, int v, int b) {
+struct HostView {
+    double c, s;  // cosine and sine of the view's angle
+};
+inline HostView host_view(const dect_geometry& g, int v) {
     const double t = g.angle0 + (double)v * g.span / (double)g.n_views;
-    const double c = std::cos(t), s = std::sin(t);
+    return {std::cos(t), std::sin(t)};
+}
+inline HostRay host_ray(const dect_geometry& g, HostView view, int b) {
+    const double c = view.c, s = view.s;
     const double u = ((double)b - 0.5 * (double)(g.n_det - 1) + g.det_offset) * g.det_cm;
     double ox, oy, dx, dy;
     if (g.kind == DECT_PARALLEL) {
@@ -66,9 +72,10 @@ inline HostRay host_ray(const dect_geometry& g, int v, int b) {
 
 // Projector workgroups: 64 / views consecutive bins of `views` consecutive base views
 // (lane = bin * views + view; views = 1, 2, 4, 8, ..., 64), so the lanes of a wave read
-// nearby image rows at every step.  Measured at 512^2 / 720 x 1024 with 8 waves, each
-// taking its share of the lines the workgroup's rays cross: 1 view (64 bins) 147 us,
-// 2 views (32 bins) 120 us, 4 views 141 us, 8 views 145 us; the tuner chooses per plan.
+// nearby image rows at every step; with two rays per lane 32 / views bins of 4 views base
+// views.  Measured at 512^2 / 720 x 1024, two FP32 channels, 8 waves, each taking its share
+// of the lines the workgroup's rays cross: 1 view 87 us, 2 views 79 us, 4 views 93 us,
+// 8 views 118 us; the tuner chooses per plan.
 constexpr int kProjViewsDefault = 2;
 DECT_HD inline bool proj_views_ok(int views) {
     return views >= 1 && views <= 64 && (views & (views - 1)) == 0;
@@ -76,15 +83,29 @@ DECT_HD inline bool proj_views_ok(int views) {
 DECT_HD inline int proj_grid_x(int D, int views) { return (D + 64 / views - 1) / (64 / views); }
 DECT_HD inline int proj_grid_y(int Vb, int views) { return (Vb + views - 1) / views; }
 
+inline HostRay host_ray(const dect_geometry& g, int v, int b) {
+    return host_ray(g, host_view(g, v), b);
+}
+
+// Rays per lane of a projector launch: two share each staged line while that leaves every
+// compute unit enough waves (the slice's own grid decides, so a batch sums as its slices do):
+// 8 for 64-byte records (256^2, four FP32 channels: 40 us against 42 us with one ray), 16
+// for shorter ones (256^2, one FP64 channel: 29 us against 25).  Wide double-precision
+// records keep to one (registers).
+inline int proj_rays(int record_bytes, int Vb, int D, int views, int waves) {
+    if (record_bytes > 64 || views > 32) return 1;
+    const long all = (long)proj_grid_x(D, 2 * views) * proj_grid_y(Vb, 4 * views) * waves;
+    return all >= 256l * (record_bytes == 64 ? 8 : 16) ? 2 : 1;
+}
+
 // Projector workgroup order.  The dispatcher hands consecutive workgroup ids to the
 // kXcds XCDs in turn, each with its own L2.  The gx bin groups form chunks of `chunk`;
 // XCD x takes chunks x, x + kXcds, ... and runs every view group of a chunk before the
 // next one.  The rays in flight on one XCD then pass through a few narrow annuli of the
 // image, whose part of the orbit images its L2 can hold, and each XCD still gets bins
 // from across the whole detector, so the XCDs' shares of ray length balance.
-// Measured at 512^2 / 720 x 1024: chunks of 1, 2, 4, 8 and 16 bin groups (of 8 bins,
-// 8 views per wave) took 146, 149, 153, 160 and 244 us against 163 us in the plain
-// bins-then-views order; 16 leaves one chunk per XCD and unequal ray lengths.
+// Measured at 512^2 / 720 x 1024, two FP32 channels: chunks of 1, 2, 4, 8 and 16 bin groups
+// (of 16 bins) took 79, 76, 79, 117 and 193 us; from 8 on the XCDs' ray lengths are unequal.
 constexpr int kXcds = 8;
 constexpr int kProjChunkDefault = 1;
 // Workgroups of one slice's projector launch (a multiple of kXcds; ids whose chunk

@@ -218,180 +218,221 @@ __device__ inline double lane_value(double x, int l) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// R for base rays: QUAD = true writes [Vb][D][SYM][CH] records, false writes the
-// standard [V][D][CH] layout (view v + k*Vb for rotation k).  A workgroup owns
-// 64 / views consecutive bins of `views` consecutive base views (one ray per lane),
-// in the XCD-aware order of proj_blocks; its KS waves step through KS
-// disjoint ranges of the image lines its rays cross (so the lanes of a wave read
-// one image line together) and wave 0 adds the KS partial sums in order.
-template <typename T, int CH, int SYM, bool QUAD, int KS, bool BATCH>
+// 16 bytes (or the record, if shorter) of a line at a byte offset, zeros past its end: the
+// buffer's bounds check extends the line by zeros on both sides (an offset below zero wraps
+// far past the end).
+template <typename U>
+__device__ inline U line_load(__amdgpu_buffer_rsrc_t line, unsigned off) {
+    U o;
+    if constexpr (sizeof(U) == 16) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(line, (int)off, 0, 0);
+        __builtin_memcpy(&o, &x, sizeof(U));
+    } else if constexpr (sizeof(U) == 8) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b64(line, (int)off, 0, 0);
+        __builtin_memcpy(&o, &x, sizeof(U));
+    } else {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b32(line, (int)off, 0, 0);
+        __builtin_memcpy(&o, &x, sizeof(U));
+    }
+    return o;
+}
+
+// R for base rays: QUAD = true writes [Vb][D][SYM][CH] records, false writes the standard
+// [V][D][CH] layout (view v + k*Vb for rotation k).  A workgroup owns the rays of 64 / BV
+// consecutive bins and RPL BV consecutive base views, BV = RPL views (RPL rays per lane, BV
+// views apart), that step along one axis, by the plan's workgroup list (XCD-aware, long
+// workgroups first); its KS waves step through KS disjoint ranges of the image
+// lines its rays cross (so the lanes of a wave read one image line together) and the waves'
+// partial sums are added in order.
+//
+// Per line a wave stages the kProjWin taps around its mean trajectory in LDS, one orbit
+// record per lane in pieces of up to 16 bytes held in separate arrays (16-byte records put
+// records r and r + 16, not r + 8, on the same banks), the next line's loads in flight while
+// the current one is summed.  Taps past the image's edge are staged as zeros, so a sample's
+// weights are those of plain linear interpolation.  LDS takes 13.8 cycles for the write of a
+// 16-byte piece by a wave and 4.6 for a read (measured), so a record's two writes cost more
+// than a ray's four reads: RPL = 2 halves the writes, loads and loop overhead per ray.
+// Measured at 512^2 / 720 x 1024, FP32, two channels: 78 us against 101 us
+// with one ray per lane and workgroups of both axes; 350 views of 512 bins, parallel, one
+// channel: 36 us against 61.  What bounds it now is LDS (38 % of the waves' time waits for it).
+template <typename T, int CH, int SYM, bool QUAD, int KS, int RPL, bool BATCH>
 __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restrict__ dev,
                                                      ProjArgs<T> one) {
     constexpr int W = CH * SYM;
     using V = vec<T, W>;
-    // Each wave's staged line window, a tap record split into NCH chunks of up to 16
-    // bytes held in separate arrays: the lanes of a wave read nearby records, and
-    // 16-byte records put records r and r + 8 (not r + 4) on the same LDS banks.
-    // After the sample loops wave w > 0 leaves its partial sums in its own window for
-    // wave 0.
-    constexpr int CE = W * (int)sizeof(T) > 16 ? 16 / (int)sizeof(T) : W;  // values per chunk
+    constexpr int CE = W * (int)sizeof(T) > 16 ? 16 / (int)sizeof(T) : W;  // values per piece
     constexpr int NCH = W / CE;
     using VC = vec<T, CE>;
     __shared__ VC s_win[KS][NCH][kProjWin];
     const ProjArgs<T> A = pick_args<BATCH>(dev, one);
     const int nx = A.nx, ny = A.ny, Vb = A.Vb, D = A.D;
-    const int BV = A.views, lbv = __builtin_ctz((unsigned)A.views);
+    const int BV = RPL * A.views, lbv = __builtin_ctz((unsigned)BV);
     const int BB = 64 >> lbv;
-    int bg, vg;
-    proj_tile(blockIdx.x, proj_grid_y(Vb, BV), A.chunk, bg, vg);
-    if (bg >= proj_grid_x(D, BV)) return;  // past the last bin group of this slice
+    if ((int)blockIdx.x >= A.blocks[RPL - 1]) return;  // beyond this slice
+    const int entry = A.order[RPL - 1][blockIdx.x], gy = proj_grid_y(Vb, BV * RPL);
+    if (entry < 0) return;
+    // The tile (bin group bg, view group vg) and the axis of the rays served.
+    const int ax = entry & 1, bg = (entry >> 1) / gy, vg = (entry >> 1) % gy;
+    const int n_steps = ax == 0 ? nx : ny;  // samples along a ray
+    const int wl = ax == 0 ? ny : nx;       // interpolation axis
+    const V* __restrict__ img = reinterpret_cast<const V*>(ax == 0 ? A.OT : A.O);
     const RayParam<T>* __restrict__ rays = A.rays;
-    const vec<T, W>* __restrict__ O = reinterpret_cast<const vec<T, W>*>(A.O);
-    const vec<T, W>* __restrict__ OT = reinterpret_cast<const vec<T, W>*>(A.OT);
     T* __restrict__ sino = A.sino;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int v = vg * BV + (lane & (BV - 1));
     const int b = bg * BB + (lane >> lbv);
-    const bool valid = b < D && v < Vb;
-    RayParam<T> r = rays[(size_t)(v < Vb ? v : Vb - 1) * D + (b < D ? b : D - 1)];
-    const bool xs = r.pad == T(0);
-    const int n_steps = xs ? nx : ny;   // samples along the ray
-    const int n_lines = xs ? ny : nx;   // interpolation axis
-    const vec<T, W>* src = xs ? OT : O;  // [n_steps][n_lines]
-    // Outside [k0, k1] both taps of every sample are outside the image, so the
-    // restriction changes no term.
-    int k0, k1;
-    proj_ray_range<T>(r.phi0, r.slope, n_steps, n_lines, k0, k1);
-    // This wave's share of the lines: every wave holds the same 64 rays, so each
-    // computes the same union [s0, s1] of their ranges and takes its KS-th of it
-    // (an even split of all lines would leave most waves idle on short chords).
-    // An empty union gives [0, -1], so no wave enters the sample loops.
-    const bool any = valid && k0 <= k1;
-    int s0 = any ? k0 : 1 << 30, s1 = any ? k1 : -1;
+    T phi0[RPL], slope[RPL], step[RPL];  // a ray of the other axis, or none: never inside
+    bool on[RPL];
+    // The lines the workgroup's rays cross: outside a ray's range both taps of every sample
+    // are outside the image, so the restriction changes no term.  Every wave holds the same
+    // rays, so each computes the same union [s0, s1] of their ranges and takes its KS-th of
+    // it (an even split of all lines would leave most waves idle on short chords).  An empty
+    // union gives [0, -1]: no wave enters the sample loop.
+    int s0 = 1 << 30, s1 = -1;
+    bool any = false;
+    T acc[RPL][W];
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        const int v = (vg * RPL + r) * BV + (lane & (BV - 1));
+        const RayParam<T> q = rays[(size_t)(v < Vb ? v : Vb - 1) * D + (b < D ? b : D - 1)];
+        on[r] = b < D && v < Vb && (q.pad == T(0)) == (ax == 0);
+        any = any || on[r];
+        phi0[r] = on[r] ? q.phi0 : T(-1e30);
+        slope[r] = on[r] ? q.slope : T(0);
+        step[r] = q.step;
+        if (on[r]) {
+            int k0, k1;
+            proj_ray_range<T>(phi0[r], slope[r], n_steps, wl, k0, k1);
+            if (k0 <= k1) {
+                s0 = k0 < s0 ? k0 : s0;
+                s1 = k1 > s1 ? k1 : s1;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < W; ++c) acc[r][c] = T(0);
+    }
     for (int off = 32; off > 0; off >>= 1) {
         const int a = __shfl_xor(s0, off, 64), c = __shfl_xor(s1, off, 64);
         s0 = a < s0 ? a : s0;
         s1 = c > s1 ? c : s1;
     }
+    const unsigned long long who = __ballot(any);
     int c0, c1;
     proj_wave_share(s0, s1, wave, KS, c0, c1);
     c0 = __builtin_amdgcn_readfirstlane(c0);  // the same in every lane
     c1 = __builtin_amdgcn_readfirstlane(c1);
-    k0 = k0 > c0 ? k0 : c0;
-    k1 = k1 < c1 ? k1 : c1;
-    if (!valid) k1 = -1;
-    T acc[W];
+    if (c0 <= c1 && who != 0ull) {
+        // The window's trajectory: the mean of the extreme rays, the first ray of the first
+        // lane and the last of the last lane that hold one.
+        const int first = __ffsll((long long)who) - 1, last = 63 - __builtin_clzll(who);
+        T pf = phi0[0], sf = slope[0], pl = phi0[RPL - 1], sb = slope[RPL - 1];
+        if constexpr (RPL > 1) {
+            bool have_f = on[0], have_l = on[RPL - 1];
 #pragma unroll
-    for (int c = 0; c < W; ++c) acc[c] = T(0);
-    auto add = [&](T w0, const V& a0, T w1, const V& a1) {
-#pragma unroll
-        for (int c = 0; c < W; ++c) {
-            acc[c] = fma(w0, a0.v[c], acc[c]);
-            acc[c] = fma(w1, a1.v[c], acc[c]);
+            for (int r = 1; r < RPL; ++r) {
+                if (!have_f && on[r]) pf = phi0[r], sf = slope[r], have_f = true;
+                const int m = RPL - 1 - r;
+                if (!have_l && on[m]) pl = phi0[m], sb = slope[m], have_l = true;
+            }
         }
-    };
-    const unsigned long long vmask = __ballot(valid);
-    const unsigned long long xmask = __ballot(valid && xs);
-    if (vmask != 0ull && (xmask == 0ull || xmask == vmask)) {
-        // Every ray of the wave steps along the same axis: stage each line's window
-        // (proj_window) in LDS, one tap per lane, the next line's loads in flight
-        // while the current line is summed.
-        using GV = const __attribute__((address_space(1))) V;
-        GV* __restrict__ wimg = (GV*)(xmask != 0ull ? OT : O);
-        const int wl = xmask != 0ull ? ny : nx;  // this wave's interpolation axis
         int wa, wb;
-        proj_window_line<T>(lane_value(r.phi0, 0), lane_value(r.slope, 0),
-                            lane_value(r.phi0, 63), lane_value(r.slope, 63), wa, wb);
+        proj_window_line<T>(lane_value(pf, first), lane_value(sf, first), lane_value(pl, last),
+                            lane_value(sb, last), wa, wb);
         wa = __builtin_amdgcn_readfirstlane(wa);
         wb = __builtin_amdgcn_readfirstlane(wb);
-        auto load = [&](GV* q) {
-            V o;
+        const int line_bytes = wl * (int)sizeof(V);
+        auto load_line = [&](int k, int start, VC (&o)[NCH]) {
+            __amdgpu_buffer_rsrc_t line = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<V*>(img + (size_t)k * wl), 0, line_bytes, 0x00027000);
+            const unsigned off = (unsigned)(start + lane) * (unsigned)sizeof(V);
 #pragma unroll
-            for (int c = 0; c < W; ++c) o.v[c] = q->v[c];
-            return o;
+            for (int h = 0; h < NCH; ++h) o[h] = line_load<VC>(line, off + h * sizeof(VC));
         };
-        // Tap t of line k, addressed from the line's start (uniform) by a 32-bit byte
-        // offset.
-        using GC = const __attribute__((address_space(1))) char;
-        auto tap = [&](int k, int t) {
-            GC* line = (GC*)(wimg + (size_t)k * wl);
-            return load((GV*)(line + (unsigned)t * (unsigned)sizeof(V)));
-        };
-        V staged;
-        int s_next = 0;
-        if (c0 <= c1) {
-            s_next = proj_window(wa, wb, c0);
-            staged = tap(c0, min(max(s_next + lane, 0), wl - 1));
-        }
+        VC staged[NCH];
+        int s_next = proj_window(wa, wb, c0);
+        load_line(c0, s_next, staged);
         for (int k = c0; k <= c1; ++k) {
             const int s0w = s_next;
 #pragma unroll
-            for (int h = 0; h < NCH; ++h)
-#pragma unroll
-                for (int c = 0; c < CE; ++c) s_win[wave][h][lane].v[c] = staged.v[h * CE + c];
-            // LDS operations of one wave complete in order; the barrier only keeps
-            // the compiler from moving the reads above the write.
+            for (int h = 0; h < NCH; ++h) s_win[wave][h][lane] = staged[h];
+            // LDS operations of one wave complete in order; the barrier only keeps the
+            // compiler from moving the reads above the write.
             __builtin_amdgcn_wave_barrier();
             if (k < c1) {
                 s_next = proj_window(wa, wb, k + 1);
-                staged = tap(k + 1, min(max(s_next + lane, 0), wl - 1));
+                load_line(k + 1, s_next, staged);
             }
-            if (k >= k0 && k <= k1) {
-                T w0, w1;
-                const int j = proj_taps<T>(r.phi0, r.slope, (T)k, wl, w0, w1);
-                const int idx = j - s0w;
-                if ((unsigned)idx <= (unsigned)(kProjWin - 2)) {
-                    V a0, a1;
+            const T kf = (T)k;
+            bool out = false;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const T ph = fma(slope[r], kf, phi0[r]);
+                const T fl = floor(ph);
+                const T w1 = ph - fl, w0 = T(1) - w1;
+                const unsigned idx = (unsigned)((int)fl - s0w);
+                if (idx <= (unsigned)(kProjWin - 2)) {
 #pragma unroll
                     for (int h = 0; h < NCH; ++h) {
                         const VC x0 = s_win[wave][h][idx], x1 = s_win[wave][h][idx + 1];
 #pragma unroll
                         for (int c = 0; c < CE; ++c) {
-                            a0.v[h * CE + c] = x0.v[c];
-                            a1.v[h * CE + c] = x1.v[c];
+                            T& a = acc[r][h * CE + c];
+                            a = fma(w0, x0.v[c], a);
+                            a = fma(w1, x1.v[c], a);
                         }
                     }
-                    add(w0, a0, w1, a1);
                 } else {
-                    add(w0, tap(k, j), w1, tap(k, j + 1));
+                    out = out || (ph > T(-1) && ph < (T)wl);
+                }
+            }
+            if (__any(out)) {  // rays outside the window (rare): from the image itself
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    const T ph = fma(slope[r], kf, phi0[r]);
+                    const unsigned idx = (unsigned)((int)floor(ph) - s0w);
+                    if (idx > (unsigned)(kProjWin - 2) && ph > T(-1) && ph < (T)wl) {
+                        T w0, w1;
+                        const int j = proj_taps<T>(phi0[r], slope[r], kf, wl, w0, w1);
+                        const V* q = img + (size_t)k * wl + j;
+                        const V a0 = q[0], a1 = q[1];
+#pragma unroll
+                        for (int c = 0; c < W; ++c)
+                            acc[r][c] = fma(w1, a1.v[c], fma(w0, a0.v[c], acc[r][c]));
+                    }
                 }
             }
             __builtin_amdgcn_wave_barrier();
         }
-    } else {
-        // Rays of both orientations: each lane reads its own taps.
-        const V* __restrict__ img = xs ? OT : O;
-        for (int k = k0; k <= k1; ++k) {
-            T w0, w1;
-            const int j = proj_taps<T>(r.phi0, r.slope, (T)k, n_lines, w0, w1);
-            const V* line = img + (size_t)k * n_lines;
-            add(w0, line[j], w1, line[j + 1]);
-        }
     }
-    if constexpr (KS > 1) {
-        if (wave > 0)
+    // The waves' sums meet in their windows, one ray of every lane at a time; wave r % KS
+    // adds those of ray r in wave order and stores them.
 #pragma unroll
-            for (int c = 0; c < W; ++c) s_win[wave][c / CE][lane].v[c % CE] = acc[c];
+    for (int r = 0; r < RPL; ++r) {
+        if (r > 0) __syncthreads();
+#pragma unroll
+        for (int c = 0; c < W; ++c) s_win[wave][c / CE][lane].v[c % CE] = acc[r][c];
         __syncthreads();
-        if (wave != 0) return;
+        if (wave != r % KS || !on[r]) continue;
+        const int v = (vg * RPL + r) * BV + (lane & (BV - 1));
+        T sum[W];
+#pragma unroll
+        for (int c = 0; c < W; ++c) sum[c] = s_win[0][c / CE][lane].v[c % CE];
         for (int w = 1; w < KS; ++w)
 #pragma unroll
-            for (int c = 0; c < W; ++c) acc[c] += s_win[w][c / CE][lane].v[c % CE];
-    }
-    if (!valid) return;
-    if constexpr (QUAD) {
-        vec<T, W> out;
+            for (int c = 0; c < W; ++c) sum[c] += s_win[w][c / CE][lane].v[c % CE];
+        if constexpr (QUAD) {
+            V out;
 #pragma unroll
-        for (int c = 0; c < W; ++c) out.v[c] = acc[c] * r.step;
-        reinterpret_cast<vec<T, W>*>(sino)[(size_t)v * D + b] = out;
-    } else {
+            for (int c = 0; c < W; ++c) out.v[c] = sum[c] * step[r];
+            reinterpret_cast<V*>(sino)[(size_t)v * D + b] = out;
+        } else {
 #pragma unroll
-        for (int s = 0; s < SYM; ++s) {
-            vec<T, CH> out;
+            for (int s = 0; s < SYM; ++s) {
+                vec<T, CH> out;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) out.v[c] = acc[s * CH + c] * r.step;
-            reinterpret_cast<vec<T, CH>*>(sino)[(size_t)(v + s * Vb) * D + b] = out;
+                for (int c = 0; c < CH; ++c) out.v[c] = sum[s * CH + c] * step[r];
+                reinterpret_cast<vec<T, CH>*>(sino)[(size_t)(v + s * Vb) * D + b] = out;
+            }
         }
     }
 }
@@ -807,8 +848,7 @@ constexpr int kLineSplit = 8;
 
 template <typename T, int CH, int SYM, bool QUAD, bool BATCH, int KS>
 void project_launch(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone, const ProjArgs<T>* pdev,
-                    const ProjArgs<T>& pone, int n, long pixels, int gx, int gy, hipStream_t s,
-                    bool orbit) {
+                    const ProjArgs<T>& pone, int n, long pixels, hipStream_t s, bool orbit) {
     if (orbit) {
         ProfScope pt("orbit", s);
         if constexpr (SYM == 4) {
@@ -822,20 +862,26 @@ void project_launch(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone, const Pr
         }
     }
     ProfScope pp("project", s);
-    hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, BATCH>), dim3(proj_blocks(gx, gy, pone.chunk), 1, n), dim3(64 * KS),
-                       0, s, pdev, pone);
+    const int R = proj_rays((int)sizeof(T) * CH * SYM, pone.Vb, pone.D, pone.views, KS);
+    const dim3 g((unsigned)std::max(pone.grid, pone.blocks[R - 1]), 1, n);
+    if constexpr (sizeof(T) * CH * SYM <= 64)
+        if (R == 2) {
+            hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 2, BATCH>), g, dim3(64 * KS), 0, s,
+                               pdev, pone);
+            return;
+        }
+    hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 1, BATCH>), g, dim3(64 * KS), 0, s, pdev,
+                       pone);
 }
 
 template <typename T, int CH, int SYM, bool QUAD, int KS>
 hipError_t project_t(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone,
-                     const ProjArgs<T>* pdev, const ProjArgs<T>& pone, int n, long pixels, int gx,
-                     int gy, hipStream_t s, bool orbit = true) {
+                     const ProjArgs<T>* pdev, const ProjArgs<T>& pone, int n, long pixels,
+                     hipStream_t s, bool orbit = true) {
     if (odev)
-        project_launch<T, CH, SYM, QUAD, true, KS>(odev, oone, pdev, pone, n, pixels, gx, gy, s,
-                                                   orbit);
+        project_launch<T, CH, SYM, QUAD, true, KS>(odev, oone, pdev, pone, n, pixels, s, orbit);
     else
-        project_launch<T, CH, SYM, QUAD, false, KS>(odev, oone, pdev, pone, n, pixels, gx, gy, s,
-                                                    orbit);
+        project_launch<T, CH, SYM, QUAD, false, KS>(odev, oone, pdev, pone, n, pixels, s, orbit);
     return hipGetLastError();
 }
 
@@ -949,11 +995,11 @@ hipError_t bp_admm(int waves, int epi, const BpArgs<T>* dev, const BpArgs<T>& on
 template <typename T, int SYM>
 hipError_t project_pair_w(int waves, const OrbitArgs<T>* odev, const OrbitArgs<T>& oone,
                           const ProjArgs<T>* pdev, const ProjArgs<T>& pone, int n, long pixels,
-                          int gx, int gy, hipStream_t s, bool orbit) {
+                          hipStream_t s, bool orbit) {
     switch (waves) {
-        case 2: return project_t<T, 2, SYM, true, 2>(odev, oone, pdev, pone, n, pixels, gx, gy, s, orbit);
-        case 4: return project_t<T, 2, SYM, true, 4>(odev, oone, pdev, pone, n, pixels, gx, gy, s, orbit);
-        case 8: return project_t<T, 2, SYM, true, 8>(odev, oone, pdev, pone, n, pixels, gx, gy, s, orbit);
+        case 2: return project_t<T, 2, SYM, true, 2>(odev, oone, pdev, pone, n, pixels, s, orbit);
+        case 4: return project_t<T, 2, SYM, true, 4>(odev, oone, pdev, pone, n, pixels, s, orbit);
+        case 8: return project_t<T, 2, SYM, true, 8>(odev, oone, pdev, pone, n, pixels, s, orbit);
     }
     return hipErrorInvalidValue;
 }
@@ -968,12 +1014,10 @@ const char* bp_name(int epi) {
 
 template <typename T>
 void fill_bp_plan(const dect_plan* p, BpArgs<T>& a) {
-    a.rays = static_cast<const RayParam<T>*>(p->rays);
     a.brays = static_cast<const BpRay<T>*>(p->bp_rays);
     a.views = static_cast<const ViewParam<T>*>(p->views);
     a.nx = p->nx;
     a.ny = p->ny;
-    a.V = p->V;
     a.Vb = p->Vb;
     a.D = p->D;
     const int dx = p->sym == 4 ? p->nx / 2 : p->nx, dy = p->sym == 4 ? p->ny / 2 : p->ny;
@@ -991,19 +1035,19 @@ hipError_t launch_project_with(const dect_plan* p, const void* img, void* sino, 
     T* OT = static_cast<T*>(OT_);
     OrbitArgs<T> o{static_cast<const T*>(img), O, OT, p->nx, p->ny};
     ProjArgs<T> q{static_cast<const RayParam<T>*>(p->rays), O, OT, static_cast<T*>(sino), p->nx,
-                  p->ny, p->Vb, p->D, p->pj_views, p->pj_chunk};
-    const int gx = proj_grid_x(p->D, p->pj_views), gy = proj_grid_y(p->Vb, p->pj_views);
+                  p->ny, p->Vb, p->D, p->pj_views, {p->pj_order[0], p->pj_order[1]},
+                  {p->pj_blocks[0], p->pj_blocks[1]}, 0};
     if (p->sym == 4) {
         switch (ch) {
-            case 1: return project_t<T, 1, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
-            case 2: return project_t<T, 2, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
-            case 4: return project_t<T, 4, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
+            case 1: return project_t<T, 1, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
+            case 2: return project_t<T, 2, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
+            case 4: return project_t<T, 4, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
         }
     } else {
         switch (ch) {
-            case 1: return project_t<T, 1, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
-            case 2: return project_t<T, 2, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
-            case 4: return project_t<T, 4, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, gx, gy, s);
+            case 1: return project_t<T, 1, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
+            case 2: return project_t<T, 2, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
+            case 4: return project_t<T, 4, 1, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);
         }
     }
     return hipErrorInvalidValue;
@@ -1017,11 +1061,11 @@ hipError_t launch_project(const dect_plan* p, const void* img, void* sino, int c
 template <typename T>
 hipError_t launch_project_pair(int sym, int waves, const OrbitArgs<T>* odev,
                                const OrbitArgs<T>& oone, const ProjArgs<T>* pdev,
-                               const ProjArgs<T>& pone, int n, long pixels, int gx, int gy,
-                               hipStream_t s, bool orbit) {
+                               const ProjArgs<T>& pone, int n, long pixels, hipStream_t s,
+                               bool orbit) {
     return sym == 4
-               ? project_pair_w<T, 4>(waves, odev, oone, pdev, pone, n, pixels, gx, gy, s, orbit)
-               : project_pair_w<T, 1>(waves, odev, oone, pdev, pone, n, pixels, gx, gy, s, orbit);
+               ? project_pair_w<T, 4>(waves, odev, oone, pdev, pone, n, pixels, s, orbit)
+               : project_pair_w<T, 1>(waves, odev, oone, pdev, pone, n, pixels, s, orbit);
 }
 
 template <typename T>
@@ -1079,7 +1123,7 @@ hipError_t launch_backproject_admm(int sym, int waves, int epi, const BpArgs<T>*
     template hipError_t launch_project<T>(const dect_plan*, const void*, void*, int, hipStream_t); \
     template hipError_t launch_project_pair<T>(int, int, const OrbitArgs<T>*, const OrbitArgs<T>&, \
                                                const ProjArgs<T>*, const ProjArgs<T>&, int, long, \
-                                               int, int, hipStream_t, bool);                      \
+                                               hipStream_t, bool);                                \
     template hipError_t launch_rhs_orbit<T>(const BpArgs<T>*, const BpArgs<T>&,                  \
                                             const OrbitArgs<T>*, const OrbitArgs<T>&, int,       \
                                             hipStream_t);                                        \

@@ -139,11 +139,11 @@ dect_status time_candidates(dect_plan* p, hipStream_t s, dect_launch& out) {
             for (int c : kChunks) {
                 ProjArgs<T> a = J.prj;
                 a.views = v;
-                a.chunk = c;
-                const int gx = proj_grid_x(p->D, v), gy = proj_grid_y(p->Vb, v);
+                rc = proj_order_for(p, v, c, a.order, a.blocks);
+                if (rc) return done(rc);
                 Timing t;
                 rc = timed([&] { return launch_project_pair<T>(J.sym, w, nullptr, J.orb, nullptr, a,
-                                                               1, J.N, gx, gy, s); }, t);
+                                                               1, J.N, s); }, t);
                 if (rc) return done(rc);
                 if (w == kPjDefault && v == kProjViewsDefault && c == kProjChunkDefault) pj_def = t;
                 if (t.us < pj_best.us) {
@@ -187,6 +187,8 @@ dect_status dect_plan_set_launch(dect_plan* p, int bp_waves, int proj_waves, int
     if (!valid_views(proj_views) || !valid_chunk(proj_chunk))
         return fail(DECT_E_ARG, "projector views per wave must be 1, 2, 4 or 8 and the chunk "
                                 "1 to 16 (got %d, %d)", proj_views, proj_chunk);
+    const dect_status st = proj_order_for(p, proj_views, proj_chunk, p->pj_order, p->pj_blocks);
+    if (st) return st;
     p->bp_waves = bp_waves;
     p->pj_waves = proj_waves;
     p->pj_views = proj_views;
@@ -227,6 +229,9 @@ dect_status dect_plan_tune(dect_plan* p, const char* cache_path, int flags, dect
             std::fclose(f);
         }
     }
+    const dect_status ost = proj_order_for(p, best.proj_views, best.proj_chunk, p->pj_order,
+                                           p->pj_blocks);
+    if (ost) return ost;
     p->bp_waves = best.bp_waves;
     p->pj_waves = best.proj_waves;
     p->pj_views = best.proj_views;
