@@ -139,7 +139,7 @@ struct dect_plan {
     // px x py = 2^lpx x 2^lpy; absent when a padded side exceeds kMaxFft)
     bool has_precond = false;
     int px = 0, py = 0, lpx = 0, lpy = 0;
-    void* pre_filter = nullptr;  // T[py][px]
+    void* pre_filter = nullptr;  // T[px][py], both frequencies bit-reversed
     void* pre_twx = nullptr;     // T[px/2][2] twiddles exp(-2 pi i k / px)
     void* pre_twy = nullptr;     // T[py/2][2]
     void* scratch_W = nullptr;   // T[ny][px][2] work grid of dect_precondition
@@ -150,11 +150,11 @@ struct dect_plan {
     int fbp_P = 0, fbp_lg = 0;
     double fbp_delta = 0.0;      // detector spacing at the isocentre, cm
     double fbp_b0 = 0.0;         // bin index of detector coordinate 0
-    void* fbp_H = nullptr;       // T[P] filter spectrum (scaled)
+    void* fbp_H = nullptr;       // T[P] filter spectrum (scaled), bit-reversed
     void* fbp_tw = nullptr;      // T[P/2][2] twiddles
     void* fbp_view = nullptr;    // T[V][4] (di, dj, ni, nj): bin and weight of a pixel
     void* fbp_wpre = nullptr;    // T[D] fan pre-weights (1 for parallel beams)
-    void* scratch_Q = nullptr;   // T[V][D][2] filtered rows
+    void* scratch_Q = nullptr;   // T[V][D + 3][4] filtered rows as records (fbp.hip)
     // state layout (bytes)
     dect_layout layout;
     size_t off_p, off_pO, off_pOT, off_r, off_q, off_dy, off_dz, off_Rp, off_t, off_da, off_fg,

@@ -17,40 +17,54 @@
 namespace dect {
 namespace {
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_fbp_filter(const T* __restrict__ sino, int ch, int D,
-                                                    int lg, const T* __restrict__ H,
+// A filtered row as the gather reads it: per bin interval k = floor(bin), its left value and
+// the step to its right one, for k = -2 ... D with zeros off the detector (record k + 2), so
+// that any bin clamped to [-2, D] reads what it should without a test.
+template <typename T, int CH>
+struct IntervalOf {  // (q[k], q[k + 1] - q[k]), CH values each
+    typedef T type __attribute__((ext_vector_type(2 * CH)));
+};
+template <typename T, int CH>
+using Interval = typename IntervalOf<T, CH>::type;
+
+// The row's FFT, filter and inverse in registers and LDS (fftcore.h).  10 us for 720 rows of 2048
+// points, FP32 (33 us with radix-2 passes on reordered rows); the chain of seven passes and
+// their barriers bounds it, with 2.8 blocks per compute unit.
+// One view per block, two channels as one complex row.
+template <typename T, int CH>
+__global__ __launch_bounds__(256) void k_fbp_filter(const T* __restrict__ sino, int D, int lg,
+                                                    const T* __restrict__ H,
                                                     const T* __restrict__ tw,
                                                     const T* __restrict__ wpre, T* __restrict__ Q) {
     extern __shared__ char smem[];
     cx<T>* buf = reinterpret_cast<cx<T>*>(smem);
-    const int v = blockIdx.x, P = 1 << lg;
-    const T* row = sino + (size_t)v * D * ch;
-    for (int i = threadIdx.x; i < P; i += blockDim.x) {
-        cx<T> x{T(0), T(0)};
-        if (i < D) {
-            x.re = row[(size_t)i * ch] * wpre[i];
-            if (ch == 2) x.im = row[(size_t)i * ch + 1] * wpre[i];
-        }
-        buf[bitrev(i, lg)] = x;
-    }
-    fft_lds<T>(buf, 1, lg, tw, false);
-    for (int k = threadIdx.x; k < P; k += blockDim.x) {
-        buf[k].re *= H[k];
-        buf[k].im *= H[k];
-    }
+    const int v = blockIdx.x;
+    const T* row = sino + (size_t)v * D * CH;
+    const LdsSeq<T> l{buf, fft_buf(lg)};
+    fft_convolve<false, T>(
+        buf, 1, lg, tw,
+        [&](int, int i) {
+            cx<T> x{T(0), T(0)};
+            if (i < D) {
+                const T w = wpre[i];
+                x.re = row[(size_t)i * CH] * w;
+                if constexpr (CH == 2) x.im = row[2 * (size_t)i + 1] * w;
+            }
+            return x;
+        },
+        [&](int, int p) { return H[p]; }, l);
     __syncthreads();
-    for (int k = threadIdx.x; k < P; k += blockDim.x) {
-        const int kr = bitrev(k, lg);
-        if (k < kr) {
-            const cx<T> a = buf[k];
-            buf[k] = buf[kr];
-            buf[kr] = a;
-        }
+    Interval<T, CH>* q = reinterpret_cast<Interval<T, CH>*>(Q) + (size_t)v * (D + 3);
+    for (int r = threadIdx.x; r < D + 3; r += blockDim.x) {
+        const int k = r - 2;
+        cx<T> a{T(0), T(0)}, b{T(0), T(0)};
+        if (k >= 0 && k < D) a = l(0, k);
+        if (k >= -1 && k < D - 1) b = l(0, k + 1);
+        if constexpr (CH == 2)
+            q[r] = Interval<T, CH>{a.re, a.im, b.re - a.re, b.im - a.im};
+        else
+            q[r] = Interval<T, CH>{a.re, b.re - a.re};
     }
-    fft_lds<T>(buf, 1, lg, tw, true);
-    cx<T>* q = reinterpret_cast<cx<T>*>(Q) + (size_t)v * D;
-    for (int b = threadIdx.x; b < D; b += blockDim.x) q[b] = buf[b];
 }
 
 template <typename T>
@@ -61,43 +75,185 @@ __device__ inline T recip(T d) {
         return T(1) / d;
 }
 
-// One thread per pixel of a 16 x 16 tile (the tile's pixels read a narrow band of
-// bins per view, which stays in L1); the views are walked in order.
-template <typename T, bool FAN>
-__global__ __launch_bounds__(256) void k_fbp_back(const T* __restrict__ Q, int nx, int ny, int V,
-                                                  int D, T b0, const T* __restrict__ view,
-                                                  T dtheta, int ch, T* __restrict__ img) {
-    const int i = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int j = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (i >= nx || j >= ny) return;
-    const T ic = (T)i - T(0.5) * (T)(nx - 1), jc = (T)j - T(0.5) * (T)(ny - 1);
-    const cx<T>* q = reinterpret_cast<const cx<T>*>(Q);
-    T ac = T(0), ap = T(0);
-#pragma unroll 4
-    for (int v = 0; v < V; ++v) {
-        const T* e = view + 4 * v;
-        T r = T(1), w = T(1);
-        if constexpr (FAN) {
-            r = recip<T>(fma(e[1], jc, fma(e[0], ic, T(1))));
-            w = r * r;
+constexpr int kFbpWin = 64;         // staged intervals of a window, one per lane
+constexpr float kFbpNear = 0.015625f;  // least U, and largest |bin|, of a staged window: the
+constexpr float kFbpFar = 16384.0f;    // bins of its pixels are then good to half a bin
+
+// The gather of FBP, on a tile of 8 x 8 PX pixels per workgroup (per orbit domain on a
+// quarter-turn symmetric plan) whose VS waves take equal shares of the views and add up at
+// the end.  For a view a wave stages in LDS the intervals its tile can reach, between the
+// extremes of the tile's corners (a projective bin is monotone along lines while U > 0), one
+// per lane; a view that needs more, or whose corners come too near the source, is read from
+// memory.  SYM = 4: base view v sees pixel rot_a(p) at the same bin and weight as view v + k
+// Vb sees rot_(a+k)(p), so each bin and weight serves four views (k) and goes into four
+// pixels' sums; views an even and an odd number of turns on each take the bin and weight that
+// they would round to by themselves (two forms of one sum: bins differ by 1e-4 between them,
+// which is what single precision can tell).  The next window's loads are in flight while one is used.
+//
+// Per pixel and view: 11 vector instructions on a symmetric plan (37 where every pixel read
+// its two taps from memory behind four comparisons, one thread per pixel walking all views)
+// and an LDS read of 16 bytes (FP32, two channels).  FBP with its filter, FP32, two channels:
+// 512^2 / 720 x 1024 fan 104 us (229 before), 366^2 / 540 x 545 parallel 62 us (149), 1024^2 /
+// 1440 x 2048 569 us (1435); instruction issue and LDS reads, about equally, bound it.
+template <typename T, int CH, int SYM, bool FAN, int VS, int PX>
+__global__ __launch_bounds__(64 * VS) void k_fbp_back(const T* __restrict__ Q, int nx, int ny,
+                                                      int Vb, int D, T b0,
+                                                      const T* __restrict__ view, T dtheta,
+                                                      T* __restrict__ img) {
+    using R = Interval<T, CH>;
+    constexpr int NV = 64 / SYM;  // views per table of windows
+    constexpr int ODD = SYM == 4 ? 2 : 1;
+    constexpr int kOut = 64 * PX * SYM * CH;
+    constexpr int kShared = VS * SYM * kFbpWin * 2 * CH > VS * kOut ? VS * SYM * kFbpWin * 2 * CH
+                                                                    : VS * kOut;
+    __shared__ __align__(32) T s_mem[kShared];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    R* win = reinterpret_cast<R*>(s_mem) + wave * SYM * kFbpWin;
+    const R* rec = reinterpret_cast<const R*>(Q);
+    const int dx = SYM == 4 ? nx / 2 : nx, dy = SYM == 4 ? ny / 2 : ny;
+    const int i0 = blockIdx.x * 8, j0 = blockIdx.y * 8 * PX;
+    const T hx = T(0.5) * (T)(nx - 1), hy = T(0.5) * (T)(ny - 1);
+    // Centred pixel coordinates; lanes past the domain repeat its last pixels.
+    const T ic = (T)min(i0 + (lane & 7), dx - 1) - hx;
+    T jc[PX];
+#pragma unroll
+    for (int p = 0; p < PX; ++p) jc[p] = (T)min(j0 + 8 * p + (lane >> 3), dy - 1) - hy;
+    const T ilo = (T)i0 - hx, ihi = (T)min(i0 + 7, dx - 1) - hx;
+    const T jlo = (T)j0 - hy, jhi = (T)min(j0 + 8 * PX - 1, dy - 1) - hy;
+    const int v0 = (int)((long)Vb * wave / VS), v1 = (int)((long)Vb * (wave + 1) / VS);
+    T acc[PX][SYM][CH] = {};
+    // odd: the order in which a view an odd number of quarter turns on rounds the same sums.
+    auto bin = [&](const T* e, T i, T j, T& r, bool odd) __attribute__((always_inline)) {
+        r = T(1);
+        if constexpr (FAN)
+            r = recip<T>(odd ? fma(e[0], i, fma(e[1], j, T(1))) : fma(e[1], j, fma(e[0], i, T(1))));
+        return fma(odd ? fma(e[2], i, e[3] * j) : fma(e[3], j, e[2] * i), r, b0);
+    };
+    auto turned = [](int a, T i, T j, T& ti, T& tj) {  // rot_a of a centred pixel
+        ti = a == 0 ? i : a == 1 ? -j : a == 2 ? -i : j;
+        tj = a == 0 ? j : a == 1 ? i : a == 2 ? -j : -i;
+    };
+#pragma unroll 1
+    for (int vc = v0; vc < v1; vc += NV) {
+        const int nv = min(NV, v1 - vc);
+        // Lane: the window of view vc + lane / SYM, rotation lane % SYM.
+        int first = 0, count = 0;
+        {
+            const T* e = view + 4 * (vc + min(lane / SYM, nv - 1));
+            const int a = lane % SYM;
+            T lo = T(0), hi = T(0), umin = T(1);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                T ti, tj, r;
+                turned(a, c & 1 ? ihi : ilo, c & 2 ? jhi : jlo, ti, tj);
+                const T b = bin(e, ti, tj, r, false);
+                const T u = fma(e[1], tj, fma(e[0], ti, T(1)));
+                lo = c == 0 || b < lo ? b : lo;
+                hi = c == 0 || b > hi ? b : hi;
+                umin = c == 0 || u < umin ? u : umin;
+            }
+            const bool ok = umin >= (T)kFbpNear && lo >= -(T)kFbpFar && hi <= (T)kFbpFar;
+            if (ok) {
+                first = (int)floor(lo) - 1;
+                count = (int)floor(hi) + 2 - first;
+                if (count > kFbpWin) count = 0;  // 0: read from memory
+            }
         }
-        const T b = fma(fma(e[3], jc, e[2] * ic), r, b0);
-        const T fb = floor(b);
-        const T al = b - fb;
-        const int k = (int)fb;
-        cx<T> q0{T(0), T(0)}, q1{T(0), T(0)};
-        const cx<T>* row = q + (size_t)v * D;
-        if (k >= 0 && k < D) q0 = row[k];
-        if (k + 1 >= 0 && k + 1 < D) q1 = row[k + 1];
-        ac = fma(w, fma(al, q1.re - q0.re, q0.re), ac);
-        ap = fma(w, fma(al, q1.im - q0.im, q0.im), ap);
+        R nxt[SYM];
+        auto fetch = [&](int n) __attribute__((always_inline)) {  // window n of the table
+            const int f = __builtin_amdgcn_readlane(first, n), m = __builtin_amdgcn_readlane(count, n);
+            const int k = min(max(f + min(lane, m), -2), D) + 2;  // lanes past it: one address
+            const R* q = rec + (size_t)(vc + n / SYM) * (D + 3);
+#pragma unroll
+            for (int t = 0; t < SYM; ++t) nxt[t] = (q + (size_t)t * Vb * (D + 3))[k];
+        };
+        fetch(0);
+#pragma unroll 1
+        for (int u = 0; u < nv; ++u) {
+            T e[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) e[c] = view[4 * (vc + u) + c];
+            auto rotation = [&](auto turn) __attribute__((always_inline)) {
+                constexpr int a = decltype(turn)::value;
+                const int n = u * SYM + a;
+                const int f = __builtin_amdgcn_readlane(first, n);
+                const int m = __builtin_amdgcn_readlane(count, n);
+                __builtin_amdgcn_wave_barrier();
+                if (lane < m) {
+#pragma unroll
+                    for (int t = 0; t < SYM; ++t) win[t * kFbpWin + lane] = nxt[t];
+                }
+                __builtin_amdgcn_wave_barrier();
+                fetch(min(n + 1, nv * SYM - 1));
+#pragma unroll
+                for (int p = 0; p < PX; ++p) {
+                    T ti, tj, al[ODD], w[ODD];
+                    int at[ODD];
+                    turned(a, ic, jc[p], ti, tj);
+#pragma unroll
+                    for (int odd = 0; odd < ODD; ++odd) {
+                        T r;
+                        const T b = bin(e, ti, tj, r, odd != 0), fb = floor(b);
+                        al[odd] = b - fb;
+                        w[odd] = r * r;
+                        at[odd] = (int)fb - f;
+                    }
+                    if (m == 0) {  // from memory, through the lane's own slots
+                        const R* g = rec + (size_t)(vc + u) * (D + 3);
+#pragma unroll
+                        for (int t = 0; t < SYM; ++t) {
+                            const int k = min(max(at[t % ODD] + f, -2), D) + 2;
+                            win[t * kFbpWin + lane] = (g + (size_t)t * Vb * (D + 3))[k];
+                        }
+#pragma unroll
+                        for (int odd = 0; odd < ODD; ++odd) at[odd] = lane;
+                    }
+#pragma unroll
+                    for (int t = 0; t < SYM; ++t) {
+                        const R q = win[t * kFbpWin + at[t % ODD]];
+#pragma unroll
+                        for (int c = 0; c < CH; ++c) {
+                            T& s = acc[p][(a + t) % SYM][c];
+                            const T x = fma(al[t % ODD], q[CH + c], q[c]);
+                            s = FAN ? fma(w[t % ODD], x, s) : s + x;
+                        }
+                    }
+                    // Keeps the sums here: moved past the next windows they would hold every
+                    // interval read in registers.
+#pragma unroll
+                    for (int t = 0; t < SYM; ++t)
+#pragma unroll
+                        for (int c = 0; c < CH; ++c) asm volatile("" : "+v"(acc[p][t][c]));
+                }
+            };
+            rotation(std::integral_constant<int, 0>{});
+            if constexpr (SYM == 4) {
+                rotation(std::integral_constant<int, 1>{});
+                rotation(std::integral_constant<int, 2>{});
+                rotation(std::integral_constant<int, 3>{});
+            }
+        }
     }
-    const long pix = (long)j * nx + i;
-    if (ch == 2) {
-        img[2 * pix] = ac * dtheta;
-        img[2 * pix + 1] = ap * dtheta;
-    } else {
-        img[pix] = ac * dtheta;
+    // The waves' sums, added in order.
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PX; ++p)
+#pragma unroll
+        for (int t = 0; t < SYM; ++t)
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                s_mem[wave * kOut + ((p * SYM + t) * CH + c) * 64 + lane] = acc[p][t][c];
+    __syncthreads();
+    for (int o = threadIdx.x; o < kOut; o += 64 * VS) {
+        T s = s_mem[o];
+        for (int w = 1; w < VS; ++w) s += s_mem[w * kOut + o];
+        const int l = o & 63, c = (o >> 6) % CH, t = (o >> 6) / CH % SYM, p = (o >> 6) / (CH * SYM);
+        const int i = i0 + (l & 7), j = j0 + 8 * p + (l >> 3);
+        if (i >= dx || j >= dy) continue;
+        const int x = t == 0 ? i : t == 1 ? nx - 1 - j : t == 2 ? nx - 1 - i : j;
+        const int y = t == 0 ? j : t == 1 ? i : t == 2 ? ny - 1 - j : ny - 1 - i;
+        img[((size_t)y * nx + x) * CH + c] = s * dtheta;
     }
 }
 
@@ -167,28 +323,55 @@ __global__ __launch_bounds__(256) void k_init_t(const T* __restrict__ a, const T
     t[2 * l + 1] = a[2 * i + 1] - Rx[2 * i + 1];
 }
 
+template <typename T, int CH, int SYM, bool FAN, int VS, int PX>
+void fbp_back_as(const dect_plan* p, dim3 g, T dtheta, T* img, hipStream_t s) {
+    hipLaunchKernelGGL((k_fbp_back<T, CH, SYM, FAN, VS, PX>), g, dim3(64 * VS), 0, s,
+                       static_cast<const T*>(p->scratch_Q), p->nx, p->ny, p->Vb, p->D,
+                       (T)p->fbp_b0, static_cast<const T*>(p->fbp_view), dtheta, img);
+}
+
+template <typename T, int CH, int SYM, bool FAN>
+void fbp_back(const dect_plan* p, T dtheta, T* img, hipStream_t s) {
+    const unsigned dx = SYM == 4 ? p->nx / 2 : p->nx, dy = SYM == 4 ? p->ny / 2 : p->ny;
+    // Tall tiles stage a window for 256 pixels instead of 128 but leave half the workgroups:
+    // from two per compute unit on (one form of the sums, FP32: 366^2 parallel 62 us against 67,
+    // 1024^2 fan 504 against 551, but 512^2 fan, 256 tall tiles, 115 against 95).  Below two
+    // small ones per unit 16 waves share the views (256^2: 31 us against 34; 512^2 with 512
+    // tiles: 101 against 95).
+    const unsigned gx = (dx + 7) / 8, g2 = (dy + 15) / 16, g4 = (dy + 31) / 32;
+    if (gx * g4 >= 512)
+        fbp_back_as<T, CH, SYM, FAN, 8, 4>(p, dim3(gx, g4), dtheta, img, s);
+    else if (gx * g2 >= 512)
+        fbp_back_as<T, CH, SYM, FAN, 8, 2>(p, dim3(gx, g2), dtheta, img, s);
+    else
+        fbp_back_as<T, CH, SYM, FAN, 16, 2>(p, dim3(gx, g2), dtheta, img, s);
+}
+
+template <typename T, int CH>
+hipError_t fbp_ch(const dect_plan* p, const T* sino, T* img, hipStream_t s) {
+    const size_t lds = (size_t)fft_buf(p->fbp_lg) * sizeof(cx<T>);
+    hipLaunchKernelGGL((k_fbp_filter<T, CH>), dim3((unsigned)p->V), dim3(256), lds, s,
+                       sino, p->D, p->fbp_lg,
+                       static_cast<const T*>(p->fbp_H), static_cast<const T*>(p->fbp_tw),
+                       static_cast<const T*>(p->fbp_wpre), static_cast<T*>(p->scratch_Q));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const T dtheta = (T)(p->geom.span / p->V);
+    if (p->sym == 4)  // quarter-turn symmetric plans are fans
+        p->geom.kind == DECT_FAN ? fbp_back<T, CH, 4, true>(p, dtheta, img, s)
+                                 : fbp_back<T, CH, 4, false>(p, dtheta, img, s);
+    else
+        p->geom.kind == DECT_FAN ? fbp_back<T, CH, 1, true>(p, dtheta, img, s)
+                                 : fbp_back<T, CH, 1, false>(p, dtheta, img, s);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t fbp_t(const dect_plan* p, const void* sino, void* img, int ch, hipStream_t s) {
     ProfScope ps("fbp", s);
-    const size_t lds = (size_t)p->fbp_P * sizeof(cx<T>);
-    hipLaunchKernelGGL((k_fbp_filter<T>), dim3(p->V), dim3(256), lds, s,
-                       static_cast<const T*>(sino), ch, p->D, p->fbp_lg,
-                       static_cast<const T*>(p->fbp_H), static_cast<const T*>(p->fbp_tw),
-                       static_cast<const T*>(p->fbp_wpre), static_cast<T*>(p->scratch_Q));
-    const dim3 g((unsigned)((p->nx + 15) / 16), (unsigned)((p->ny + 15) / 16));
-    const dect_geometry& G = p->geom;
-    const T dtheta = (T)(G.span / p->V);
-    if (G.kind == DECT_FAN)
-        hipLaunchKernelGGL((k_fbp_back<T, true>), g, dim3(256), 0, s,
-                           static_cast<const T*>(p->scratch_Q), p->nx, p->ny, p->V, p->D,
-                           (T)p->fbp_b0, static_cast<const T*>(p->fbp_view), dtheta, ch,
-                           static_cast<T*>(img));
-    else
-        hipLaunchKernelGGL((k_fbp_back<T, false>), g, dim3(256), 0, s,
-                           static_cast<const T*>(p->scratch_Q), p->nx, p->ny, p->V, p->D,
-                           (T)p->fbp_b0, static_cast<const T*>(p->fbp_view), dtheta, ch,
-                           static_cast<T*>(img));
-    return hipGetLastError();
+    const T* in = static_cast<const T*>(sino);
+    return ch == 2 ? fbp_ch<T, 2>(p, in, static_cast<T*>(img), s)
+                   : fbp_ch<T, 1>(p, in, static_cast<T*>(img), s);
 }
 
 template <typename T>

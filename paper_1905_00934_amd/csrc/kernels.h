@@ -385,7 +385,7 @@ hipError_t launch_udm_batch(const UdmArgs<T>* args, int n, int blocks, bool join
 template <typename T>
 struct PrecArgs {
     int nx, ny, px, py, lpx, lpy;  // image and padded grid (px = 2^lpx, py = 2^lpy)
-    const T* filter;               // [py][px]
+    const T* filter;               // [px][py], both frequencies bit-reversed
     const T* twx;                  // [px/2][2]
     const T* twy;                  // [py/2][2]
     T* W;                          // [ny][px][2] work grid

@@ -250,8 +250,15 @@ int pad_pow2(int n, int& lg) {
     return P;
 }
 
+// The lg-bit reversal of every index below 2^lg.
+std::vector<int> bit_reversed(int lg) {
+    std::vector<int> r((size_t)1 << lg, 0);
+    for (size_t i = 1; i < r.size(); ++i) r[i] = r[i >> 1] >> 1 | (int)(i & 1) << (lg - 1);
+    return r;
+}
+
 // Preconditioner of the x-update: the floored ramp max(|w|, 1/max(Py, Px)) on the
-// zero-padded DFT grid (|w| in cycles per pixel) and the DFT twiddle factors
+// zero-padded DFT grid (|w| in cycles per pixel), bit-reversed in both axes, and the DFT twiddle factors
 // exp(-2 pi i k / P), k < P / 2, of both padded sides.
 template <typename T>
 dect_status build_precond(dect_plan* p) {
@@ -261,11 +268,12 @@ dect_status build_precond(dect_plan* p) {
     const int px = p->px, py = p->py;
     const double floor_w = 1.0 / (double)(px > py ? px : py);
     std::vector<T> filt((size_t)px * py);
-    for (int ky = 0; ky < py; ++ky) {
-        const double fy = (ky < py / 2 ? ky : ky - py) / (double)py;
-        for (int kx = 0; kx < px; ++kx) {
-            const double fx = (kx < px / 2 ? kx : kx - px) / (double)px;
-            filt[(size_t)ky * px + kx] = (T)std::fmax(std::sqrt(fx * fx + fy * fy), floor_w);
+    const std::vector<int> rx = bit_reversed(p->lpx), ry = bit_reversed(p->lpy);
+    for (int qx = 0; qx < px; ++qx) {
+        const double fx = (rx[qx] < px / 2 ? rx[qx] : rx[qx] - px) / (double)px;
+        for (int qy = 0; qy < py; ++qy) {
+            const double fy = (ry[qy] < py / 2 ? ry[qy] : ry[qy] - py) / (double)py;
+            filt[(size_t)qx * py + qy] = (T)std::fmax(std::sqrt(fx * fx + fy * fy), floor_w);
         }
     }
     dect_status st = upload<T>(filt.data(), filt.size() * sizeof(T), &p->pre_filter);
@@ -290,7 +298,7 @@ dect_status build_precond(dect_plan* p) {
 // the detector spacing delta at the isocentre, h[0] = 1/(4 delta^2), h[n] =
 // -1/(pi^2 n^2 delta^2) for odd n, zero for even n, circular over P = a power of
 // two at least twice the bins; its DFT (real and even) is stored scaled by
-// delta / P (and 1/2 for a fan over a full turn), so the filtered row is the
+// delta / P (and 1/2 for a fan over a full turn), bit-reversed, so the filtered row is the
 // inverse FFT of the product with no further factor.  Per view the (cos, sin) of
 // its angle; per bin the fan pre-weight D / sqrt(D^2 + u^2).
 template <typename T>
@@ -308,13 +316,14 @@ dect_status build_fbp(dect_plan* p) {
     h[0] = 1.0 / (4.0 * delta * delta);
     for (int n = 1; n <= P / 2; n += 2) h[n] = -1.0 / (pi * pi * (double)n * n * delta * delta);
     std::vector<T> H(P);
+    const std::vector<int> rev = bit_reversed(p->fbp_lg);
     const double scale = delta / P * (fan ? 0.5 : 1.0);
     for (int k = 0; k < P; ++k) {
         // h is even: H[k] = h[0] + 2 sum_{0 < n < P/2} h[n] cos(2 pi k n / P) + h[P/2] cos(pi k).
         double acc = h[0];
         for (int n = 1; n < P / 2; n += 2) acc += 2.0 * h[n] * std::cos(2.0 * pi * (double)k * n / P);
         acc += h[P / 2] * ((k & 1) ? -1.0 : 1.0);
-        H[k] = (T)(acc * scale);
+        H[rev[k]] = (T)(acc * scale);
     }
     dect_status st = upload<T>(H.data(), H.size() * sizeof(T), &p->fbp_H);
     if (st) return st;
@@ -353,7 +362,7 @@ dect_status build_fbp(dect_plan* p) {
     }
     st = upload<T>(wpre.data(), wpre.size() * sizeof(T), &p->fbp_wpre);
     if (st) return st;
-    DECT_HIP(hipMalloc(&p->scratch_Q, (size_t)V * D * 2 * sizeof(T)));
+    DECT_HIP(hipMalloc(&p->scratch_Q, (size_t)V * (D + 3) * 4 * sizeof(T)));
     p->has_fbp = true;
     return DECT_OK;
 }
