@@ -99,7 +99,9 @@ struct JointTab {
 // s kept the evaluation in range: every sum finite (no A_k overflowed) and both
 // normalising sums at least 2^-90, so that terms lost below 2^-126 are below 2^-36 of
 // their sum.
-template <typename T, int U = 4>
+// Eight records are read at once: with four, a lone wave waited on each group of scalar loads
+// (an a-update of 64^2 / 90 x 128, FP32, 12.7 us against 13.8; 512^2 43.8 against 45.3).
+template <typename T, int U = 8>
 __device__ inline bool spectra_eval_joint(const JointTab<T>& J, T ac, T ap, T s, T& fh, T& ghc,
                                           T& ghp, T& fl, T& glc, T& glp) {
     using CT = const __attribute__((address_space(4))) T;
@@ -221,6 +223,18 @@ __device__ inline T det2(T a, T d, T b, T c) {
     return f + e;
 }
 
+// Trial points that a workgroup of NT rays evaluates together (lm_solve): the points
+// asked for, packed, and per ray the last evaluation of its trial point.
+template <typename T, int NT>
+struct EvalPack {
+    T in[3][NT];    // a_c, a_p, shift
+    T last[3][NT];  // the same per ray, of its last evaluation
+    unsigned short ray[NT];
+    T out[6][NT];  // f_h, its gradient, f_l, its gradient
+    unsigned char ok[NT];
+    int count[3];  // points of an iteration, in turn
+};
+
 // m Levenberg-Marquardt iterations from P (evaluated); P ends at the last accepted
 // point.  A trial point is evaluated in one pass, shifted by the log-sum-exp of
 // the current point: the exponents then change by at most
@@ -235,22 +249,80 @@ __device__ inline T det2(T a, T d, T b, T c) {
 // lm_solve together.  Without a joint table (a weight below 2^-24 of its spectrum) the
 // spectra are evaluated apart.
 //
+// NT > 1 (with JT; the workgroup's rays): a ray whose iteration has the trial point and shift of its last evaluation
+// takes that evaluation's result, which would come out the same bit for bit.  This is what
+// most iterations of a converged ray are: its step is a few units of the point's last place
+// and rejected, and the growing damping leaves point and shift as they were (over 20
+// constrained iterations of a 512^2 slice, FP32, 61 % of the evaluations; 15 % of 10
+// unconstrained ones).  A wave seldom has no ray left that moves, so the workgroup's rays
+// that do are packed into as few waves as they fill, the first of them another one each
+// iteration and workgroup, as the waves of a workgroup sit on different SIMDs.  20 iterations
+// at 512^2 / 720 x 1024, FP32: 391 us against 563 with every ray evaluating each of its own;
+// what is left is a third each the evaluations, the two-pass one of the start, and the steps.
+//
 // CONSTR (the constrained decomposition, a >= 0): a coordinate at zero whose
 // gradient is positive is held at zero and the damped step is taken in the other
 // coordinate alone; trial points are projected onto a >= 0.
 //
 // accepted: bit k set when LM iteration k (k < 32) accepted its trial point.
-template <typename T, bool CONSTR, bool JT>
-__device__ inline void lm_solve(const T* __restrict__ spec, int kmax, int kh, int kl,
-                                const JointTab<T>& jt, T mh, T ml, T wh, T wl, T vc, T vp,
+template <typename T, bool CONSTR, bool JT, int NT>
+__device__ inline void lm_solve(EvalPack<T, NT>* pack, const T* __restrict__ spec, int kmax,
+                                int kh, int kl, const JointTab<T>& jt, T mh, T ml, T wh, T wl, T vc, T vp,
                                 T rc, T rp, int iters, T mu, StepBound sb, Point<T>& P,
                                 unsigned& accepted) {
     constexpr T log2e = T(1.4426950408889634);
+    constexpr bool PACK = NT > 1;
     accepted = 0u;
     // The iterations are predicated rather than left early, so that all lanes of a wave
     // reach the spectra evaluation together (the joint path's fallback is wave-wide).
     bool stop = false;  // CONSTR: stationary at the corner
+    int turn = 0;
+    if constexpr (PACK) {
+        if (threadIdx.x < 3) pack->count[threadIdx.x] = 0;
+        pack->last[2][threadIdx.x] = NAN;  // equal to no shift
+        __syncthreads();
+    }
+    // The points asked for by the workgroup's rays, evaluated into pack->out and pack->ok.
+    auto evaluate_packed = [&](int it, bool ask, T ac, T ap, T s) {
+        EvalPack<T, NT>& E = *pack;
+        const int me = (int)threadIdx.x, lane = me & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(me >> 6);
+        const unsigned long long asks = __ballot(ask);
+        int base = 0;
+        if (lane == 0 && asks) base = atomicAdd(&E.count[turn], __popcll(asks));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (ask) {
+            const int n = base + __popcll(asks & ((1ull << lane) - 1));
+            E.in[0][n] = E.last[0][me] = ac;
+            E.in[1][n] = E.last[1][me] = ap;
+            E.in[2][n] = E.last[2][me] = s;
+            E.ray[n] = (unsigned short)me;
+        }
+        __syncthreads();
+        const int total = E.count[turn];
+        turn = turn == 2 ? 0 : turn + 1;
+        // Last read two iterations ago, next used in the next one.
+        if (me == 0) E.count[turn] = 0;
+        const int first = (int)((wave + it + blockIdx.x) % (NT / 64)) * 64;
+        if (first < total) {
+            const int n = min(first + lane, total - 1), r = E.ray[n];
+            T f[6];
+            const bool in_range = spectra_eval_joint<T>(jt, E.in[0][n], E.in[1][n], E.in[2][n],
+                                                            f[0], f[1], f[2], f[3], f[4], f[5]);
+            if (first + lane < total) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) E.out[k][r] = f[k];
+                E.ok[r] = in_range;
+            }
+        }
+        __syncthreads();
+    };
     for (int it = 0; it < iters; ++it) {
+        if constexpr (PACK)
+            if (__all(stop)) {  // nothing to ask for, but others' points to evaluate
+                evaluate_packed(it, false, T(0), T(0), T(0));
+                continue;
+            }
         const T rh = P.fh - mh, rl = P.fl - ml;
         const T Gc = wh * rh * P.ghc + wl * rl * P.glc + rc * (P.ac - vc);
         const T Gp = wh * rh * P.ghp + wl * rl * P.glp + rp * (P.ap - vp);
@@ -311,8 +383,23 @@ __device__ inline void lm_solve(const T* __restrict__ spec, int kmax, int kh, in
             const T ll = -(P.fl + P.glc * dc + P.glp * dp) * log2e;
             const T s = fmin(fmax(T(0.5) * (lh + ll), fmax(sh, sl) + up - (T)jt.lim),
                              fmin(lh, ll) + T(90));
-            const bool ok =
-                spectra_eval_joint<T>(jt, Q.ac, Q.ap, s, Q.fh, Q.ghc, Q.ghp, Q.fl, Q.glc, Q.glp);
+            bool ok;
+            if constexpr (PACK) {
+                const int me = (int)threadIdx.x;
+                EvalPack<T, NT>& E = *pack;
+                evaluate_packed(it, !skip && !(Q.ac == E.last[0][me] && Q.ap == E.last[1][me] &&
+                                               s == E.last[2][me]), Q.ac, Q.ap, s);
+                Q.fh = E.out[0][me];
+                Q.ghc = E.out[1][me];
+                Q.ghp = E.out[2][me];
+                Q.fl = E.out[3][me];
+                Q.glc = E.out[4][me];
+                Q.glp = E.out[5][me];
+                ok = E.ok[me];
+            } else {
+                ok = spectra_eval_joint<T>(jt, Q.ac, Q.ap, s, Q.fh, Q.ghc, Q.ghp, Q.fl, Q.glc,
+                                           Q.glp);
+            }
             // A ray whose sums left the range is evaluated again by the whole wave, its
             // bins spread over the lanes, so that a few such rays do not hold up the wave.
             unsigned long long need = __ballot(!ok && !skip);
@@ -335,6 +422,16 @@ __device__ inline void lm_solve(const T* __restrict__ spec, int kmax, int kh, in
                     Q.fl = f0;
                     Q.glc = g0;
                     Q.glp = g1;
+                    if constexpr (PACK) {
+                        const int me = (int)threadIdx.x;
+                        pack->out[0][me] = Q.fh;
+                        pack->out[1][me] = Q.ghc;
+                        pack->out[2][me] = Q.ghp;
+                        pack->out[3][me] = Q.fl;
+                        pack->out[4][me] = Q.glc;
+                        pack->out[5][me] = Q.glp;
+                        pack->ok[me] = 1;
+                    }
                 }
             }
             const T rh = Q.fh - mh, rl = Q.fl - ml, ec = Q.ac - vc, ep = Q.ap - vp;
@@ -357,9 +454,11 @@ __device__ inline void lm_solve(const T* __restrict__ spec, int kmax, int kh, in
     }
 }
 
-// JT: the plan has a joint table (joint_lim > 0); see lm_solve.
-template <typename T, int MODE, bool BATCH, bool JT>
-__global__ __launch_bounds__(256) void k_udm(const UdmArgs<T>* __restrict__ dev, UdmArgs<T> one) {
+// JT: the plan has a joint table (joint_lim > 0); PACK: the rays of a workgroup that packs its
+// trial points, 0 if it does not; see lm_solve.
+template <typename T, int MODE, bool BATCH, bool JT, int PACK = 0>
+__global__ __launch_bounds__(PACK ? PACK : 256, PACK && sizeof(T) == 4 ? 8 : 1) void k_udm(
+    const UdmArgs<T>* __restrict__ dev, UdmArgs<T> one) {
     using V2 = vec<T, 2>;
     using V4 = vec<T, 4>;
     const UdmArgs<T> A = pick_args<BATCH>(dev, one);
@@ -445,8 +544,13 @@ __global__ __launch_bounds__(256) void k_udm(const UdmArgs<T>* __restrict__ dev,
         unsigned accepted;
         const JointTab<T> jt{A.joint,  A.jb,      A.jh,      A.jl,     A.joint_lim,
                              A.jkc[0], A.jkc[1], A.jkp[0], A.jkp[1]};
-        lm_solve<T, MODE == 3, JT>(spec, kmax, kh, kl, jt, mh, ml, wh, wl, vc, vp, rc, rp, A.iters,
-                               (T)A.mu0, sb, P, accepted);
+        EvalPack<T, PACK ? PACK : 1>* pack = nullptr;
+        if constexpr (PACK > 0) {
+            __shared__ EvalPack<T, PACK> s_pack;
+            pack = &s_pack;
+        }
+        lm_solve<T, MODE == 3, JT>(pack, spec, kmax, kh, kl, jt, mh, ml, wh, wl, vc, vp, rc, rp,
+                                   A.iters, (T)A.mu0, sb, P, accepted);
         if (live) {
             if constexpr (MODE == 2) {
                 if (A.lmbits) A.lmbits[i] = (uint8_t)(accepted & 0xffu);
@@ -569,6 +673,21 @@ hipError_t launch_udm(const dect_plan* p, int mode, const UdmArgs<T>& a0, hipStr
     dim3 g((unsigned)(a.udm_blocks + tvb));
     ProfScope ps(mode == 1 ? "udm_init" : (mode == 3 ? "cdm" : "udm"), s);
     const bool jt = a.joint_lim > 0.0f;
+    // Constrained solves pack their trial points: the unconstrained start of the ADMM repeats
+    // too few (512^2 FP32, 10 iterations: 317 us against 308), a launch of less than two waves
+    // per SIMD gains nothing by idle waves (128^2: 124 us against 114).  512 rays pack tighter
+    // than 256 (512^2 FP32: 391 us against 428) but want several such workgroups per compute
+    // unit, in double precision more registers than there are (256^2: 660 us against 489).
+    if (jt && mode == 3 && a.iters >= 4 && a.M >= 131072) {
+        auto packed = [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            hipLaunchKernelGGL((k_udm<T, 3, false, true, NT>), dim3((unsigned)((a.M + NT - 1) / NT)),
+                               dim3(NT), 0, s, nullptr, a);
+        };
+        if (sizeof(T) == 4 && a.M >= 262144) packed(std::integral_constant<int, 512>{});
+        else packed(std::integral_constant<int, 256>{});
+        return hipGetLastError();
+    }
     if (mode == 0 && jt)
         hipLaunchKernelGGL((k_udm<T, 0, false, true>), g, dim3(256), 0, s, nullptr, a);
     else if (mode == 0)
