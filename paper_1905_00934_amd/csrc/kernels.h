@@ -117,6 +117,7 @@ struct BpArgs {
     int gx, gy;   // this slice's grid of 8x8 orbit blocks
     const int* order;  // [gx gy]: the block of each launch position (bp_block_order)
     const T* sino;
+    const T* weight;  // quarter-turn plans' plain transpose: ray weights of sino, or nullptr
     T* out;
     T* out2;
     const T* x;

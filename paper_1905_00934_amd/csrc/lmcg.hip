@@ -298,24 +298,27 @@ __global__ __launch_bounds__(256) void k_lm_trial_x(ImgArgs I, int b, const T* _
     block_sum_store<4>(v, part + (size_t)blockIdx.x * kPartialSlots);
 }
 
+// The accepted trial point: blocks below sino_blocks take the rays' R x and f cache, the
+// others the image (one launch: two took 5.9 and 4.7 us at 384^2 / 540 x 768, FP32, mostly
+// their start and end).
 template <typename T>
-__global__ __launch_bounds__(256) void k_lm_accept_img(long N, const double* __restrict__ sc,
-                                                       const T* __restrict__ xt,
-                                                       T* __restrict__ x) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < N && sc[L_ACC] != 0.0) x[k] = xt[k];
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_lm_accept_sino(long M, const double* __restrict__ sc,
-                                                        const T* __restrict__ at,
-                                                        const T* __restrict__ ft,
-                                                        T* __restrict__ Rx, T* __restrict__ fc) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M || sc[L_ACC] == 0.0) return;
-    Rx[i] = at[i];
+__global__ __launch_bounds__(256) void k_lm_accept(long M, long N, int sino_blocks,
+                                                   const double* __restrict__ sc,
+                                                   const T* __restrict__ at,
+                                                   const T* __restrict__ ft, T* __restrict__ Rx,
+                                                   T* __restrict__ fc, const T* __restrict__ xt,
+                                                   T* __restrict__ x) {
+    if (sc[L_ACC] == 0.0) return;
+    if ((int)blockIdx.x < sino_blocks) {
+        const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+        if (i >= M) return;
+        Rx[i] = at[i];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) fc[c * M + i] = ft[c * M + i];
+        for (int c = 0; c < 6; ++c) fc[c * M + i] = ft[c * M + i];
+    } else {
+        const long k = ((long)blockIdx.x - sino_blocks) * blockDim.x + threadIdx.x;
+        if (k < N) x[k] = xt[k];
+    }
 }
 
 // y = shrink(D x - u^y, lambda / rho), z = max(0, x - u^z), u^y += y - D x, u^z += z - x
@@ -578,9 +581,11 @@ LmPtrs<T> lm_ptrs(const LmLayout& L, void* st) {
 }
 
 template <typename T>
-hipError_t bp1(const dect_plan* p, const T* sino, T* img, hipStream_t s) {
+hipError_t bp1(const dect_plan* p, const T* sino, T* img, hipStream_t s,
+               const T* weight = nullptr) {
     BpArgs<T> a{};
     a.sino = sino;
+    a.weight = weight;
     a.out = img;
     return launch_backproject<T>(p, 1, a, s);
 }
@@ -629,11 +634,11 @@ hipError_t lm_iteration(const dect_plan* p, const LmLayout& L, const LmPtrs<T>& 
             }
             for (int c = 0; c < prm->cg_iters; ++c) {
                 LM_TRY(launch_project<T>(p, P.pv, P.Rp, 1, s));
-                {
+                if (p->sym != 4) {  // else the transpose's reordering multiplies
                     ProfScope ps("lm_vec", s);
                     hipLaunchKernelGGL((k_lm_wmul<T>), gs, b256, 0, s, M, P.W, P.Rp);
                 }
-                LM_TRY(bp1<T>(p, P.Rp, P.tmp, s));
+                LM_TRY(bp1<T>(p, P.Rp, P.tmp, s, p->sym == 4 ? P.W : nullptr));
                 ProfScope ps("lm_vec", s);
                 hipLaunchKernelGGL((k_lm_hp<T>), gi, b256, 0, s, I, b, P.tmp, P.pv, P.sc, P.q,
                                    P.pimg);
@@ -641,7 +646,8 @@ hipError_t lm_iteration(const dect_plan* p, const LmLayout& L, const LmPtrs<T>& 
                 hipLaunchKernelGGL((k_lm_step<T>), gi, b256, 0, s, N, P.sc, P.pv, P.q, P.d, P.r,
                                    P.pimg);
                 hipLaunchKernelGGL(k_lm_reduce, dim3(1), b256, 0, s, R, (int)LR_UPD, 0);
-                hipLaunchKernelGGL((k_lm_dir<T>), gi, b256, 0, s, N, P.sc, P.r, P.pv);
+                if (c + 1 < prm->cg_iters)  // the last step leaves no direction to take
+                    hipLaunchKernelGGL((k_lm_dir<T>), gi, b256, 0, s, N, P.sc, P.r, P.pv);
             }
             {
                 ProfScope ps("lm_vec", s);
@@ -652,9 +658,8 @@ hipError_t lm_iteration(const dect_plan* p, const LmLayout& L, const LmPtrs<T>& 
             LM_TRY(launch_lm_eval<T>(p, b, P.at, Rxo, mh, ml, wh, wl, P.ft, P.psino, s));
             ProfScope ps("lm_vec", s);
             hipLaunchKernelGGL(k_lm_reduce, dim3(1), b256, 0, s, R, (int)LR_TRIAL, 0);
-            hipLaunchKernelGGL((k_lm_accept_img<T>), gi, b256, 0, s, N, P.sc, P.xt, xb);
-            hipLaunchKernelGGL((k_lm_accept_sino<T>), gs, b256, 0, s, M, P.sc, P.at, P.ft, Rxb,
-                               P.fc);
+            hipLaunchKernelGGL((k_lm_accept<T>), dim3(gs.x + gi.x), b256, 0, s, M, N, (int)gs.x,
+                               P.sc, P.at, P.ft, Rxb, P.fc, P.xt, xb);
         }
     }
     ProfScope ps("lm_tv", s);

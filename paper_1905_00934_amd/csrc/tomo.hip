@@ -886,10 +886,11 @@ hipError_t project_t(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone,
 }
 
 // A standard [V][D][CH] sinogram as quad records [Vb][D][4][CH] (view v + k Vb is
-// rotation k of base view v), the layout the transpose of a quarter-turn symmetric plan
-// reads: one record per thread, the four views' rows read and the records written along b.
+// rotation k of base view v), times the ray weights if there are any, the layout the
+// transpose of a quarter-turn symmetric plan reads: one record per thread, the four views' rows read and the records written along b.
 template <typename T, int CH>
-__global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino, int Vb, int D,
+__global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino,
+                                                      const T* __restrict__ weight, int Vb, int D,
                                                       T* __restrict__ quad) {
     const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;  // (vb, b)
     const long rows = (long)Vb * D;
@@ -900,6 +901,10 @@ __global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino
         const vec<T, CH> t = reinterpret_cast<const vec<T, CH>*>(sino)[r + k * rows];
 #pragma unroll
         for (int c = 0; c < CH; ++c) o.v[k * CH + c] = t.v[c];
+        if (weight) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) o.v[k * CH + c] *= weight[r + k * rows];
+        }
     }
     reinterpret_cast<vec<T, 4 * CH>*>(quad)[r] = o;
 }
@@ -913,7 +918,7 @@ hipError_t bp_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
     if constexpr (SYM == 4) {
         const long recs = (long)one.Vb * one.D;
         hipLaunchKernelGGL((k_quad_records<T, CH>), dim3((unsigned)((recs + 255) / 256)), dim3(256),
-                           0, s, one.sino, one.Vb, one.D, quad);
+                           0, s, one.sino, one.weight, one.Vb, one.D, quad);
         a.sino = quad;
     }
     hipLaunchKernelGGL((k_backproject<T, CH, SYM, EPI_NONE, VS, false>), dim3(one.gx * one.gy),
