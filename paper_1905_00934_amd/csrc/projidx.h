@@ -90,10 +90,9 @@ inline HostRay host_ray(const dect_geometry& g, int v, int b) {
 // Rays per lane of a projector launch: two share each staged line while that leaves every
 // compute unit enough waves (the slice's own grid decides, so a batch sums as its slices do):
 // 8 for 64-byte records (256^2, four FP32 channels: 40 us against 42 us with one ray), 16
-// for shorter ones (256^2, one FP64 channel: 29 us against 25).  Wide double-precision
-// records keep to one (registers).
+// for shorter ones (256^2, one FP64 channel: 29 us against 25).
 inline int proj_rays(int record_bytes, int Vb, int D, int views, int waves) {
-    if (record_bytes > 64 || views > 32) return 1;
+    if (views > 32) return 1;
     const long all = (long)proj_grid_x(D, 2 * views) * proj_grid_y(Vb, 4 * views) * waves;
     return all >= 256l * (record_bytes == 64 ? 8 : 16) ? 2 : 1;
 }

@@ -255,10 +255,22 @@ __device__ inline U line_load(__amdgpu_buffer_rsrc_t line, unsigned off) {
 // Measured at 512^2 / 720 x 1024, FP32, two channels: 78 us against 101 us
 // with one ray per lane and workgroups of both axes; 350 views of 512 bins, parallel, one
 // channel: 36 us against 61.  What bounds it now is LDS (38 % of the waves' time waits for it).
+//
+// Records of 128 bytes (four FP64 channels, quarter-turn symmetric) go in two halves of two
+// rotations, a workgroup each (blockIdx.y): 512^2 598 us, 256^2 91 us against 805 and 137
+// whole, whose eight pieces of LDS leave room for half the waves and whose sums for none to
+// share a line.
+template <typename T, int W>
+constexpr int proj_parts() {
+    return (int)sizeof(T) * W > 64 ? 2 : 1;
+}
+
 template <typename T, int CH, int SYM, bool QUAD, int KS, int RPL, bool BATCH>
 __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restrict__ dev,
                                                      ProjArgs<T> one) {
-    constexpr int W = CH * SYM;
+    constexpr int PARTS = proj_parts<T, CH * SYM>(), SP = SYM / PARTS, W = CH * SP;
+    static_assert(!QUAD || PARTS == 1, "quad records are written whole");
+    const int part = PARTS == 1 ? 0 : (int)blockIdx.y;  // rotations part SP ... of each record
     using V = vec<T, W>;
     constexpr int CE = W * (int)sizeof(T) > 16 ? 16 / (int)sizeof(T) : W;  // values per piece
     constexpr int NCH = W / CE;
@@ -275,7 +287,7 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
     const int ax = entry & 1, bg = (entry >> 1) / gy, vg = (entry >> 1) % gy;
     const int n_steps = ax == 0 ? nx : ny;  // samples along a ray
     const int wl = ax == 0 ? ny : nx;       // interpolation axis
-    const V* __restrict__ img = reinterpret_cast<const V*>(ax == 0 ? A.OT : A.O);
+    const V* __restrict__ img = reinterpret_cast<const V*>(ax == 0 ? A.OT : A.O) + part;
     const RayParam<T>* __restrict__ rays = A.rays;
     T* __restrict__ sino = A.sino;
     const int lane = threadIdx.x & 63;
@@ -340,11 +352,11 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
                             lane_value(sb, last), wa, wb);
         wa = __builtin_amdgcn_readfirstlane(wa);
         wb = __builtin_amdgcn_readfirstlane(wb);
-        const int line_bytes = wl * (int)sizeof(V);
+        const int line_bytes = (wl * PARTS - part) * (int)sizeof(V);
         auto load_line = [&](int k, int start, VC (&o)[NCH]) {
             __amdgpu_buffer_rsrc_t line = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<V*>(img + (size_t)k * wl), 0, line_bytes, 0x00027000);
-            const unsigned off = (unsigned)(start + lane) * (unsigned)sizeof(V);
+                const_cast<V*>(img + (size_t)k * wl * PARTS), 0, line_bytes, 0x00027000);
+            const unsigned off = (unsigned)(start + lane) * (unsigned)(PARTS * sizeof(V));
 #pragma unroll
             for (int h = 0; h < NCH; ++h) o[h] = line_load<VC>(line, off + h * sizeof(VC));
         };
@@ -393,8 +405,8 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
                     if (idx > (unsigned)(kProjWin - 2) && ph > T(-1) && ph < (T)wl) {
                         T w0, w1;
                         const int j = proj_taps<T>(phi0[r], slope[r], kf, wl, w0, w1);
-                        const V* q = img + (size_t)k * wl + j;
-                        const V a0 = q[0], a1 = q[1];
+                        const V* q = img + ((size_t)k * wl + j) * PARTS;
+                        const V a0 = q[0], a1 = q[PARTS];
 #pragma unroll
                         for (int c = 0; c < W; ++c)
                             acc[r][c] = fma(w1, a1.v[c], fma(w0, a0.v[c], acc[r][c]));
@@ -427,11 +439,11 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
             reinterpret_cast<V*>(sino)[(size_t)v * D + b] = out;
         } else {
 #pragma unroll
-            for (int s = 0; s < SYM; ++s) {
+            for (int s = 0; s < SP; ++s) {
                 vec<T, CH> out;
 #pragma unroll
                 for (int c = 0; c < CH; ++c) out.v[c] = sum[s * CH + c] * step[r];
-                reinterpret_cast<vec<T, CH>*>(sino)[(size_t)(v + s * Vb) * D + b] = out;
+                reinterpret_cast<vec<T, CH>*>(sino)[(size_t)(v + (part * SP + s) * Vb) * D + b] = out;
             }
         }
     }
@@ -862,16 +874,15 @@ void project_launch(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone, const Pr
         }
     }
     ProfScope pp("project", s);
-    const int R = proj_rays((int)sizeof(T) * CH * SYM, pone.Vb, pone.D, pone.views, KS);
-    const dim3 g((unsigned)std::max(pone.grid, pone.blocks[R - 1]), 1, n);
-    if constexpr (sizeof(T) * CH * SYM <= 64)
-        if (R == 2) {
-            hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 2, BATCH>), g, dim3(64 * KS), 0, s,
-                               pdev, pone);
-            return;
-        }
-    hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 1, BATCH>), g, dim3(64 * KS), 0, s, pdev,
-                       pone);
+    constexpr int PARTS = proj_parts<T, CH * SYM>();
+    const int R = proj_rays((int)sizeof(T) * CH * SYM / PARTS, pone.Vb, pone.D, pone.views, KS);
+    const dim3 g((unsigned)std::max(pone.grid, pone.blocks[R - 1]), PARTS, n);
+    if (R == 2)
+        hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 2, BATCH>), g, dim3(64 * KS), 0, s,
+                           pdev, pone);
+    else
+        hipLaunchKernelGGL((k_project<T, CH, SYM, QUAD, KS, 1, BATCH>), g, dim3(64 * KS), 0, s,
+                           pdev, pone);
 }
 
 template <typename T, int CH, int SYM, bool QUAD, int KS>
