@@ -27,7 +27,7 @@ HBM_PEAK_GBS = 8000.0
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "admm_fan512_hbm_traffic.txt")
 KERNEL_SOURCES = ["tomo.hip", "udm.hip", "admm.hip", "kernels.h", "common.h", "epilogue.h", "tv.h",
-                  "reduce.h", "projidx.h"]
+                  "reduce.h", "projidx.h", "bpidx.h"]
 
 
 def kernel_source_hash() -> str:
@@ -82,11 +82,11 @@ def binding_unit(kernel: str) -> dict | None:
             rows[parts[0]] = {"valu_busy": float(parts[4]), "ta_busy": float(parts[6])}
     if meta.get("source_hash") != kernel_source_hash():
         return None
-    # The FP32 ADMM instantiations (two channels, quarter-turn symmetry, quad records;
-    # the transposes' q and dual epilogues with single-precision sums).
+    # The FP32 ADMM instantiations (two channels, quarter-turn symmetry, quad records; the
+    # transposes' q and dual epilogues with single-precision sums).
     pick = {"project": ("k_project<float,2,4,true,", ">"),
-            "backproject_q": ("k_backproject<float,2,4,true,2,", ",float>"),
-            "backproject_dual": ("k_backproject<float,2,4,true,3,", ",float>")}.get(kernel)
+            "backproject_q": ("k_backproject<float,2,4,2,", ",float>"),
+            "backproject_dual": ("k_backproject<float,2,4,3,", ",float>")}.get(kernel)
     for k, v in rows.items():
         if pick and k.startswith(pick[0]) and k.endswith(pick[1]):
             unit = "texture addresser (vector-memory path)" if v["ta_busy"] >= v["valu_busy"] \

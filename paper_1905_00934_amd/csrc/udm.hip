@@ -315,7 +315,7 @@ struct EvalPack {
 // that do are packed into as few waves as they fill, the first of them another one each
 // iteration and workgroup, as the waves of a workgroup sit on different SIMDs.  20 iterations
 // at 512^2 / 720 x 1024, FP32: 391 us against 563 with every ray evaluating each of its own;
-// what is left is a third each the evaluations, the two-pass one of the start, and the steps.
+// what is left is, by iteration counts, 170 us of evaluations, 130 of steps, 60 of the start.
 //
 // CONSTR (the constrained decomposition, a >= 0): a coordinate at zero whose
 // gradient is positive is held at zero and the damped step is taken in the other
