@@ -7,7 +7,7 @@
 // views as exact rotations of the V/4 base views (SYM = 4): one Joseph weight
 // computation serves four views.  Otherwise SYM = 1 and every view is a base view.
 //
-// Projector: one lane per base ray; a wave holds consecutive bins of one to four
+// Projector: one or two base rays per lane; a wave holds consecutive bins of a few
 // neighbouring base views, so output writes are coalesced along the detector.  It
 // reads an "orbit" image O[j][i] = (X[rot^k (i, j)], k < SYM) -- the SYM rotated
 // copies interleaved per pixel -- or its transpose for x-stepped rays, so that one
@@ -17,9 +17,8 @@
 // Transpose: one lane owns the rotation orbit of a pixel.  For every base view
 // and every orbit member it locates the bins whose samples can touch the pixel and
 // re-evaluates each candidate's interpolation weight from the same ray geometry;
-// each weight serves SYM (pixel, view) pairs.  The projector forms the two tap
-// weights of a sample as tents max(0, 1 - |phi - j|) and scales by the step length at
-// the end, while the transpose forms each weight step max(0, 1 - |d|) from the
+// each weight serves SYM (pixel, view) pairs.  The projector interpolates between a
+// sample's two taps by the fraction of its position and scales by the step length at the end, while the transpose forms each weight step max(0, 1 - |d|) from the
 // signed distance d of its own ray records, so the pair is a transpose up to rounding
 // (FP64 adjointness to 1e-12), not bit for bit.  The views are split over the waves
 // of a workgroup and the wave sums are added in a fixed order through LDS.
@@ -939,8 +938,8 @@ hipError_t bp_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
 
 // Waves per workgroup of a transpose launch: the plan's choice, doubled (to at most 16) while
 // the slice's blocks would leave a compute unit fewer than 64 waves: at 256^2 (256 blocks)
-// 4, 8 and 16 waves took 58, 38 and 31 us, at 512^2 8 and 16 waves the same 107 us.  It hangs on the slice's blocks alone, so a batch
-// sums as its slices do.  Wide double-precision records keep to 8 (registers).
+// 4, 8 and 16 waves took 58, 38 and 31 us, at 512^2 8 and 16 waves the same 107 us.  It hangs
+// on the slice's blocks alone, so a batch sums as its slices do.  Wide double-precision records keep to 8 (registers).
 template <typename T, int W>
 int bp_waves_for(int waves, int blocks) {
     const int most = sizeof(T) == 8 && W > 4 ? 8 : 16;
