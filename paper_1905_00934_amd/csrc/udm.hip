@@ -630,51 +630,34 @@ __global__ __launch_bounds__(PACK ? PACK : 256, PACK && sizeof(T) == 4 ? 8 : 1) 
 // f and its gradient of both spectra at (a_c, a_p) = (at, ao) (basis 0) or (ao, at)
 // (basis 1), for the LM x CG scheme: cache[k][M], k = (f_h, f_l, df_h/da_c,
 // df_h/da_p, df_l/da_c, df_l/da_p); block partials of 1/2 sum_s w_s (f_s - m_s)^2.
-//
-// JT (the plan has a joint table): one exponential per bin for both spectra, with the shift
-// of lm_solve for a step from a = 0, where f = 0 and the gradients are the spectra's means;
-// a ray it does not fit is evaluated exactly by its whole wave.  384^2 / 540 x 768, FP32:
-// 20 us against 32 with two passes over each spectrum.
-struct MeanGrad {
-    double hc, hp, lc, lp;
-};
-template <typename T, bool JT>
-__global__ __launch_bounds__(256) void k_lm_eval(
-    const T* __restrict__ spec, int kmax, int kh, int kl, JointTab<T> jt, MeanGrad g0, long M,
-    int basis, const T* __restrict__ at, const T* __restrict__ ao, const T* __restrict__ mh,
-    const T* __restrict__ ml, const T* __restrict__ wh, const T* __restrict__ wl,
-    T* __restrict__ cache, double* __restrict__ partials) {
-    const long i0 = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = i0 < M;
+// Each spectrum's largest exponent is the shift: one shift for both spectra from the joint
+// table (20 us against 32 at 384^2 / 540 x 768, FP32) lies further from their log-sum-exps, and
+// the images came out up to 1.6 times further from double precision.
+template <typename T>
+__global__ __launch_bounds__(256) void k_lm_eval(const T* __restrict__ spec, int kmax, int kh,
+                                                 int kl, long M, int basis,
+                                                 const T* __restrict__ at,
+                                                 const T* __restrict__ ao, const T* __restrict__ mh,
+                                                 const T* __restrict__ ml, const T* __restrict__ wh,
+                                                 const T* __restrict__ wl, T* __restrict__ cache,
+                                                 double* __restrict__ partials) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (live || JT) {
-        const long i = live ? i0 : M - 1;
+    if (i < M) {
         Point<T> P;
         P.ac = basis == 0 ? at[i] : ao[i];
         P.ap = basis == 0 ? ao[i] : at[i];
-        if constexpr (JT) {
-            constexpr T log2e = T(1.4426950408889634);
-            const T lh = -((T)g0.hc * P.ac + (T)g0.hp * P.ap) * log2e;
-            const T ll = -((T)g0.lc * P.ac + (T)g0.lp * P.ap) * log2e;
-            const T s = joint_shift<T>(jt, P.ac, P.ap, T(0), T(0), lh, ll);
-            const bool ok =
-                spectra_eval_joint<T>(jt, P.ac, P.ap, s, P.fh, P.ghc, P.ghp, P.fl, P.glc, P.glp);
-            wave_eval_exact<T>(spec, kmax, kh, kl, !ok, P);
-        } else {
-            evaluate<T>(spec, kmax, kh, kl, mh[i], ml[i], wh[i], wl[i], T(0), T(0), T(0), T(0),
-                        T(0), T(0), true, P);
-        }
-        if (live) {
-            cache[i] = P.fh;
-            cache[M + i] = P.fl;
-            cache[2 * M + i] = P.ghc;
-            cache[3 * M + i] = P.ghp;
-            cache[4 * M + i] = P.glc;
-            cache[5 * M + i] = P.glp;
-            const double eh = (double)P.fh - (double)mh[i], el = (double)P.fl - (double)ml[i];
-            v[0] = 0.5 * ((double)wh[i] * eh * eh + (double)wl[i] * el * el);
-            v[1] = (isfinite(P.fh) && isfinite(P.fl)) ? 0.0 : 1.0;
-        }
+        evaluate<T>(spec, kmax, kh, kl, mh[i], ml[i], wh[i], wl[i], T(0), T(0), T(0), T(0), T(0),
+                    T(0), true, P);
+        cache[i] = P.fh;
+        cache[M + i] = P.fl;
+        cache[2 * M + i] = P.ghc;
+        cache[3 * M + i] = P.ghp;
+        cache[4 * M + i] = P.glc;
+        cache[5 * M + i] = P.glp;
+        const double eh = (double)P.fh - (double)mh[i], el = (double)P.fl - (double)ml[i];
+        v[0] = 0.5 * ((double)wh[i] * eh * eh + (double)wl[i] * el * el);
+        v[1] = (isfinite(P.fh) && isfinite(P.fl)) ? 0.0 : 1.0;
     }
     block_sum_store<4>(v, partials + (size_t)blockIdx.x * kPartialSlots);
 }
@@ -774,18 +757,9 @@ hipError_t launch_lm_eval(const dect_plan* p, int basis, const T* at, const T* a
                           const T* ml, const T* wh, const T* wl, T* cache, double* partials,
                           hipStream_t s) {
     ProfScope ps("lm_eval", s);
-    UdmArgs<T> a{};
-    fill_udm_tables<T>(p, a);
-    const JointTab<T> jt{a.joint,  a.jb,     a.jh,     a.jl,    a.joint_lim,
-                         a.jkc[0], a.jkc[1], a.jkp[0], a.jkp[1]};
-    const MeanGrad g{p->mean_f[0][0], p->mean_f[0][1], p->mean_f[1][0], p->mean_f[1][1]};
-    const dim3 blocks((unsigned)((p->M + 255) / 256));
-    if (a.joint_lim > 0.0f)
-        hipLaunchKernelGGL((k_lm_eval<T, true>), blocks, dim3(256), 0, s, a.spec, a.kmax, a.kh,
-                           a.kl, jt, g, p->M, basis, at, ao, mh, ml, wh, wl, cache, partials);
-    else
-        hipLaunchKernelGGL((k_lm_eval<T, false>), blocks, dim3(256), 0, s, a.spec, a.kmax, a.kh,
-                           a.kl, jt, g, p->M, basis, at, ao, mh, ml, wh, wl, cache, partials);
+    hipLaunchKernelGGL((k_lm_eval<T>), dim3((unsigned)((p->M + 255) / 256)), dim3(256), 0, s,
+                       static_cast<const T*>(p->spec), p->kmax, p->kh, p->kl, p->M, basis, at, ao,
+                       mh, ml, wh, wl, cache, partials);
     return hipGetLastError();
 }
 
