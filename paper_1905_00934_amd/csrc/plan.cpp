@@ -42,18 +42,24 @@ dect_status upload(const void* host, size_t bytes, void** dev) {
     return DECT_OK;
 }
 
-// The same beside a stream capture of this thread: no call that a capture refuses, no work on
-// the default stream.
-dect_status upload_aside(const void* host, size_t bytes, void** dev) {
+// The same on `device`, whatever device is current, beside a stream capture of this thread: no
+// call that a capture refuses, no work on the default stream.
+dect_status upload_aside(int device, const void* host, size_t bytes, void** dev) {
+    int current = -1;
+    DECT_HIP(hipGetDevice(&current));
+    if (current != device) DECT_HIP(hipSetDevice(device));
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    DECT_HIP(hipThreadExchangeStreamCaptureMode(&mode));
     hipStream_t s = nullptr;
-    hipError_t e = hipMalloc(dev, bytes);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipMemcpyAsync(*dev, host, bytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (s) (void)hipStreamDestroy(s);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
+        e = hipMalloc(dev, bytes);
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipMemcpyAsync(*dev, host, bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (s) (void)hipStreamDestroy(s);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (current != device) (void)hipSetDevice(current);
     DECT_HIP(e);
     return DECT_OK;
 }
@@ -416,8 +422,8 @@ void make_layout(dect_plan* p) {
 
 }  // namespace
 
-// Kept per shape, at most 64 of them.  A shape may be chosen while a stream is captured: the
-// copy then runs on a stream of its own, outside the capture.
+// Kept per shape, at most 64 of them.  A shape may be chosen while a stream is captured (the
+// copy then runs on a stream of its own, outside the capture) or another device is current.
 dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&order)[2],
                            int (&blocks)[2]) {
     const dect_plan::ProjOrder* hit = nullptr;
@@ -428,7 +434,7 @@ dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&orde
         for (int R = 1; R <= 2 && R * views <= 64; ++R) {
             const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
                                                          R * views, R * R * views, chunk);
-            const dect_status st = upload_aside(t.data(), t.size() * sizeof(int),
+            const dect_status st = upload_aside(p->device, t.data(), t.size() * sizeof(int),
                                                 reinterpret_cast<void**>(&o.order[R - 1]));
             if (st) {
                 (void)hipFree(o.order[0]);
