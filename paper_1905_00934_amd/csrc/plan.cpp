@@ -431,19 +431,25 @@ dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&orde
         if (o.views == views && o.chunk == chunk) hit = &o;
     if (!hit) {
         dect_plan::ProjOrder o{views, chunk, {nullptr, nullptr}, {0, 0}};
-        for (int R = 1; R <= 2 && R * views <= 64; ++R) {
-            const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
-                                                         R * views, R * R * views, chunk);
-            const dect_status st = upload_aside(p->device, t.data(), t.size() * sizeof(int),
-                                                reinterpret_cast<void**>(&o.order[R - 1]));
-            if (st) {
-                (void)hipFree(o.order[0]);
-                (void)hipFree(o.order[1]);
-                return st;
+        dect_status st = DECT_OK;
+        try {
+            p->pj_orders.reserve(p->pj_orders.size() + 1);
+            for (int R = 1; R <= 2 && R * views <= 64 && st == DECT_OK; ++R) {
+                const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
+                                                             R * views, R * R * views, chunk);
+                st = upload_aside(p->device, t.data(), t.size() * sizeof(int),
+                                  reinterpret_cast<void**>(&o.order[R - 1]));
+                o.blocks[R - 1] = (int)t.size();
             }
-            o.blocks[R - 1] = (int)t.size();
+        } catch (const std::bad_alloc&) {
+            st = fail(DECT_E_NOMEM, "host allocation failed");
         }
-        p->pj_orders.push_back(o);
+        if (st != DECT_OK) {
+            (void)hipFree(o.order[0]);
+            (void)hipFree(o.order[1]);
+            return st;
+        }
+        p->pj_orders.push_back(o);  // reserved above
         hit = &p->pj_orders.back();
     }
     for (int r = 0; r < 2; ++r) {
@@ -527,11 +533,18 @@ dect_status dect_plan_create(const dect_geometry* geom, const dect_spectra* spec
         delete p;
         return fail(DECT_E_DEVICE, "no HIP device");
     }
-    dect_status st = dtype == DECT_F32 ? build_tables<float>(p, spec) : build_tables<double>(p, spec);
-    if (st == DECT_OK) st = build_block_order(p);
-    if (st == DECT_OK) st = proj_order_for(p, p->pj_views, p->pj_chunk, p->pj_order, p->pj_blocks);
-    if (st == DECT_OK) st = dtype == DECT_F32 ? build_precond<float>(p) : build_precond<double>(p);
-    if (st == DECT_OK) st = dtype == DECT_F32 ? build_fbp<float>(p) : build_fbp<double>(p);
+    dect_status st = DECT_OK;
+    try {
+        st = dtype == DECT_F32 ? build_tables<float>(p, spec) : build_tables<double>(p, spec);
+        if (st == DECT_OK) st = build_block_order(p);
+        if (st == DECT_OK)
+            st = proj_order_for(p, p->pj_views, p->pj_chunk, p->pj_order, p->pj_blocks);
+        if (st == DECT_OK)
+            st = dtype == DECT_F32 ? build_precond<float>(p) : build_precond<double>(p);
+        if (st == DECT_OK) st = dtype == DECT_F32 ? build_fbp<float>(p) : build_fbp<double>(p);
+    } catch (const std::bad_alloc&) {
+        st = fail(DECT_E_NOMEM, "host allocation failed");
+    }
     if (st == DECT_OK && hipMalloc(reinterpret_cast<void**>(&p->scratch_part),
                                    (size_t)(p->ny > kRaySumBlocks ? p->ny : kRaySumBlocks + 1) *
                                        kPartialSlots *

@@ -1,14 +1,18 @@
 // The plan's host code (plan.cpp) over a HIP runtime of its own that keeps memory on the host
 // and knows which device every allocation and stream belongs to.  Plain C++, no GPU.
 //
-// usage: plan_host device
+// usage: plan_host device | nomem
 //   device: the projector's lists go to the plan's device whatever device is current, which
 //           stays current
+//   nomem:  lists or a plan that host memory does not suffice for are an error, not an
+//           exception, and nothing leaks
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <set>
+#include <utility>
 
 #include "common.h"
 
@@ -16,18 +20,34 @@ namespace {
 int g_current = 0, g_bad = 0;
 std::map<void*, int> g_memory;  // allocation -> device
 std::set<hipStream_t> g_streams;
+long g_fail_after = -1;  // host allocations left before one fails; -1: none does
 
 void expect(bool ok, const char* what) {
     if (!ok) std::printf("failed: %s\n", what), ++g_bad;
 }
+void* host_alloc(std::size_t n) {
+    if (g_fail_after >= 0 && g_fail_after-- == 0) return nullptr;
+    return std::malloc(n ? n : 1);
+}
 }  // namespace
+
+void* operator new(std::size_t n) {
+    if (void* p = host_alloc(n)) return p;
+    throw std::bad_alloc();
+}
+// A sort's buffer may be missing: it then does without.
+void* operator new(std::size_t n, const std::nothrow_t&) noexcept { return std::malloc(n); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipGetDevice(int* d) { return *d = g_current, hipSuccess; }
 hipError_t hipSetDevice(int d) { return g_current = d, hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) {
+    const long left = std::exchange(g_fail_after, -1);  // not for this runtime's own
     *p = std::malloc(n ? n : 1);
     g_memory[*p] = g_current;
+    g_fail_after = left;
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {
@@ -41,8 +61,10 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
     return std::memcpy(d, s, n), hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    const long left = std::exchange(g_fail_after, -1);
     *s = reinterpret_cast<hipStream_t>(new int(g_current));
     g_streams.insert(*s);
+    g_fail_after = left;
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t s) {
@@ -76,7 +98,7 @@ int main(int argc, char** argv) {
     dect_plan* p = nullptr;
     g_current = 1;
     expect(dect_plan_create(&g, &spec, DECT_F32, &p) == DECT_OK, "plan");
-    const auto before = g_memory;
+    auto before = g_memory;
     const int* order[2] = {nullptr, nullptr};
     int blocks[2] = {0, 0};
     if (argc > 1 && !std::strcmp(argv[1], "device")) {
@@ -89,6 +111,39 @@ int main(int argc, char** argv) {
             made += before.count(m.first) == 0;
         }
         expect(made == 2, "two lists");
+    } else {
+        // Each host allocation of the two calls in turn fails.
+        for (int call = 0; call < 2; ++call) {
+            long fails = 0;
+            dect_plan* q = nullptr;
+            for (long n = 0; !g_bad; ++n) {
+                g_fail_after = n;
+                dect_status st = DECT_E_DEVICE;
+                try {
+                    st = call == 0 ? proj_order_for(p, 8, 2, order, blocks)
+                                   : dect_plan_create(&g, &spec, DECT_F64, &q);
+                } catch (...) {
+                    expect(false, "nothing is thrown");
+                }
+                const bool failed = g_fail_after < 0;
+                g_fail_after = -1;
+                if (!failed) {
+                    expect(st == DECT_OK, "the call succeeds");
+                    break;
+                }
+                ++fails;
+                expect(st == DECT_E_NOMEM, "out of memory is reported");
+                expect(call == 1 ? !q : !order[0] && !order[1] && !blocks[0], "no result");
+                expect(g_streams.empty() && g_memory == before, "nothing leaks");
+            }
+            expect(fails > 0, "allocations failed");
+            if (call == 0) {
+                expect(order[0] && order[1] && blocks[0] > 0, "lists");
+                before = g_memory;
+            } else {
+                dect_plan_destroy(q);
+            }
+        }
     }
     g_current = 1;
     dect_plan_destroy(p);

@@ -1,5 +1,5 @@
 """The plan's host code over a HIP runtime that lives on the host (tests/plan_host.cpp): which
-device its lists are put on."""
+device its lists are put on, and what a shortage of host memory does."""
 import os
 import shutil
 import subprocess
@@ -32,3 +32,7 @@ def _run(program, what):
 
 def test_projector_lists_are_on_the_plans_device(program):
     _run(program, "device")
+
+
+def test_projector_lists_without_host_memory(program):
+    _run(program, "nomem")
