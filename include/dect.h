@@ -128,9 +128,10 @@ dect_status dect_project_noalloc(const dect_plan* plan, const void* img, void* s
  * ray geometry in a different but equivalent arithmetic form (so the pair is
  * adjoint to rounding: <R x, y> = <x, R^T y> to 1e-12 relative in FP64).
  * sino: device [n_views][n_det][ch]; img: device [ny][nx][ch] (overwritten);
- * ch in {1, 2, 4}.  async.  On a quarter-turn symmetric plan the sinogram is
- * first reordered into a plan-owned scratch sinogram, so calls with one plan
- * must not run concurrently on different streams. */
+ * ch in {1, 2, 4}.  async.  On a quarter-turn symmetric plan one or two channels
+ * are first reordered into a plan-owned scratch sinogram, so such calls with one
+ * plan must not run concurrently on different streams; calls with four channels,
+ * and calls with a plan that is not symmetric, use no scratch and may. */
 dect_status dect_backproject(const dect_plan* plan, const void* sino, void* img, int ch,
                              void* stream);
 

@@ -216,7 +216,7 @@ dect_status build_tables(dect_plan* p, const dect_spectra* spec) {
     }
     DECT_HIP(hipMalloc(&p->scratch_O, (size_t)p->N * 4 * p->sym * sizeof(T)));
     DECT_HIP(hipMalloc(&p->scratch_OT, (size_t)p->N * 4 * p->sym * sizeof(T)));
-    if (p->sym == 4) DECT_HIP(hipMalloc(&p->scratch_sq, (size_t)p->M * 4 * sizeof(T)));
+    if (p->sym == 4) DECT_HIP(hipMalloc(&p->scratch_sq, (size_t)p->M * 2 * sizeof(T)));
     return DECT_OK;
 }
 

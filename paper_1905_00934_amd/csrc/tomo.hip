@@ -497,6 +497,11 @@ __device__ inline float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(
 constexpr int kBpSlots = 2;
 constexpr int kBpBatch = 64;
 
+// Sinograms of one and two channels are read by quarter-turn symmetric plans as quad records
+// ([Vb][D][SYM][CH]: one 16- or 32-byte load per record); four channels are 16-byte pieces in
+// their views' own rows already, and need no scratch copy.
+constexpr bool bp_quads(int ch, int sym) { return sym == 4 && ch < 4; }
+
 // Pieces of a staged record: the ray record in 16-byte pieces, the values in 16-byte
 // pieces or, below 16 bytes, in one piece of their size.
 template <typename T, int W>
@@ -543,12 +548,17 @@ __device__ inline void gather_windows(const BpArgs<T>& a, int wave, int lane, in
         const BpRay<T>* row = a.brays + (size_t)v * (unsigned)(D + 1);
         return load(BpRay<T>{}, row, b * (unsigned)sizeof(BpRay<T>));
     };
-    // The values of bin b of base view v in all SYM views it stands for (a record).
+    // The values of bin b of base view v in all SYM views it stands for (a record, or CH values
+    // of each view's row).
     auto values_at = [&](int v, unsigned b, T (&s)[W]) {
-        const vec<T, W> t = load(vec<T, W>{}, a.sino + (size_t)v * (unsigned)D * W,
-                                 b * (unsigned)sizeof(vec<T, W>));
+        constexpr int ROWS = bp_quads(CH, SYM) ? 1 : SYM, R = W / ROWS;
 #pragma unroll
-        for (int c = 0; c < W; ++c) s[c] = t.v[c];
+        for (int k = 0; k < ROWS; ++k) {
+            const vec<T, R> t = load(vec<T, R>{}, a.sino + (size_t)(v + k * Vb) * (unsigned)D * R,
+                                     b * (unsigned)sizeof(vec<T, R>));
+#pragma unroll
+            for (int c = 0; c < R; ++c) s[k * R + c] = t.v[c];
+        }
     };
     // Record `lane` of the window written; record o read.
     auto store = [&](const BpRay<T>& r, const T (&s)[W]) {
@@ -750,7 +760,7 @@ __device__ inline void gather_windows(const BpArgs<T>& a, int wave, int lane, in
 // R^T (+ epilogue).  A workgroup owns an 8x8 block of pixel orbits (the block
 // lies in the first quadrant when SYM = 4) and has VS waves, each summing a
 // disjoint subset of the base views.  Sinograms are records of the SYM views of a base
-// ray ([Vb][D][SYM][CH]).  A: the type the sums are kept in (T, or double for an FP32
+// ray (bp_quads) or plain.  A: the type the sums are kept in (T, or double for an FP32
 // plan's sums in double precision: each product of two FP32 values is exact in double, so
 // only the sums round); the finished values are rounded to T once.
 //
@@ -920,12 +930,13 @@ __global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino
 }
 
 // Plain R^T of a standard [V][D][CH] sinogram with `waves` waves per workgroup; on a
-// quarter-turn symmetric plan it is first reordered into quad records (plan scratch):
-// staging straight from the four views' rows measured 146 us against 105 us + 4 us.
+// quarter-turn symmetric plan one or two channels are first reordered into quad records (plan
+// scratch): staging two channels straight from the four views' rows measured 146 us against
+// 105 us + 4 us.
 template <typename T, int CH, int SYM, int VS>
 hipError_t bp_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
     BpArgs<T> a = one;
-    if constexpr (SYM == 4) {
+    if constexpr (bp_quads(CH, SYM)) {
         const long recs = (long)one.Vb * one.D;
         hipLaunchKernelGGL((k_quad_records<T, CH>), dim3((unsigned)((recs + 255) / 256)), dim3(256),
                            0, s, one.sino, one.weight, one.Vb, one.D, quad);
