@@ -499,7 +499,9 @@ constexpr int kBpBatch = 64;
 
 // Sinograms of one and two channels are read by quarter-turn symmetric plans as quad records
 // ([Vb][D][SYM][CH]: one 16- or 32-byte load per record); four channels are 16-byte pieces in
-// their views' own rows already, and need no scratch copy.
+// their views' own rows already, and read there they share no scratch between calls (FP32 and
+// FP64: 256^2 32 and 59 us against 38 and 77 us reordered, 512^2 188 and 338 against 194 and
+// 422; 1024^2 FP32 1388 against 1295).
 constexpr bool bp_quads(int ch, int sym) { return sym == 4 && ch < 4; }
 
 // Pieces of a staged record: the ray record in 16-byte pieces, the values in 16-byte
