@@ -414,6 +414,30 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
             }
             __builtin_amdgcn_wave_barrier();
         }
+        // A sum that is not finite is formed again from the taps that have weight: a ray that
+        // passes exactly over a line of pixels, or exactly one line outside the image, took the
+        // next pixel with weight zero above, and an infinity there is none of its own.
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+            bool finite = true;
+#pragma unroll
+            for (int c = 0; c < W; ++c) finite = finite && isfinite(acc[r][c]);
+            if (finite) continue;
+#pragma unroll
+            for (int c = 0; c < W; ++c) acc[r][c] = T(0);
+#pragma unroll 1
+            for (int k = c0; k <= c1; ++k) {
+                T w0, w1;
+                const int j = proj_taps<T>(phi0[r], slope[r], (T)k, wl, w0, w1);
+                const V* q = img + ((size_t)k * wl + j) * PARTS;
+                if (w0 > T(0))
+#pragma unroll
+                    for (int c = 0; c < W; ++c) acc[r][c] = fma(w0, q[0].v[c], acc[r][c]);
+                if (w1 > T(0))
+#pragma unroll
+                    for (int c = 0; c < W; ++c) acc[r][c] = fma(w1, q[PARTS].v[c], acc[r][c]);
+            }
+        }
     }
     // The waves' sums meet in their windows, one ray of every lane at a time; wave r % KS
     // adds those of ray r in wave order and stores them.
