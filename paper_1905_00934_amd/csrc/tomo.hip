@@ -509,7 +509,7 @@ __device__ inline float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(
 // A slot whose window would be too long (a block so near the source that the fan spreads
 // over more than kBpWin bins), and every slot of a wave whose sums came out non-finite
 // (zero weights must not carry a NaN or an infinity of the sinogram to other pixels), is
-// gathered candidate by candidate from global memory.
+// gathered candidate by candidate from global memory, those without weight left out.
 //
 // What bounds it: LDS and VALU issue, about equally.  Per view and 64 pixels at
 // 512^2 / 720 x 1024 (two channels, FP32) 204 VALU instructions (341 with a footprint per
@@ -754,9 +754,11 @@ __device__ inline void gather_windows(const BpArgs<T>& a, int wave, int lane, in
                     const int lo = (int)ceil(fmin(fmax(bc - h, T(0)), (T)D));
                     const int hi = (int)floor(fmax(fmin(bc + h, (T)(D - 1)), T(-1)));
                     for (int b = lo; b <= hi; ++b) {
+                        const T wt = weight(ray_at(v, (unsigned)b), fi, fj);
+                        if (!(wt > T(0))) continue;  // nothing of it, finite or not
                         T s[W];
                         values_at(v, (unsigned)b, s);
-                        add(weight(ray_at(v, (unsigned)b), fi, fj), s);
+                        add(wt, s);
                     }
                 }
 #pragma unroll
