@@ -360,7 +360,7 @@ dect_status dect_lmcg_iterate(const dect_plan* plan, const void* m_h, const void
  *  - proj_chunk: bin groups an XCD takes per turn of the workgroup order (1 to 16).
  * Defaults 4, 8, 2, 1.  Every shape computes the same sums; only the order in which a
  * workgroup's partial sums are added changes.  Batches share launches only between
- * slices whose plans have the same shapes. */
+ * slices whose plans run the same shapes (bp_waves that come to the same number agree). */
 typedef struct {
     int bp_waves;      /* transposed projector */
     int proj_waves;    /* projector */
@@ -379,7 +379,7 @@ typedef struct {
  * device, precision and problem shape, else by timing every candidate on a scratch
  * state on `stream` (synchronises; allocates a temporary state) and appending the
  * result to the cache (cache_path NULL: no cache).  Candidates: bp_waves 2, 4, 8 for
- * the transpose; proj_waves 2, 4, 8 x proj_views 1, 2, 4 x proj_chunk 1, 2, 4 for the
+ * the transpose, of those that run the same launch one; proj_waves 2, 4, 8 x proj_views 1, 2, 4 x proj_chunk 1, 2, 4 for the
  * projector; each timed as the median of 3 batches of 8 launches after 2 warm-up
  * launches.  A candidate replaces the default only if it is faster by more than the
  * larger of 1 % and the batches' spread, so run-to-run noise does not change the

@@ -247,7 +247,7 @@ SliceJob<T> make_job(const dect_plan* p, const void* mh, const void* ml, const v
     J.N = p->N;
     J.M = p->M;
     J.sym = p->sym;
-    J.bp_waves = p->bp_waves;
+    J.bp_waves = bp_waves_for(sizeof(T), 2 * p->sym, p->bp_waves, bp_blocks(p));
     J.pj_waves = p->pj_waves;
     J.pj_views = p->pj_views;
     J.pj_chunk = p->pj_chunk;

@@ -303,8 +303,19 @@ hipError_t launch_rhs_orbit(const BpArgs<T>* dev, const BpArgs<T>& one, const Or
 // Plain R^T of a standard-order sinogram with ch channels (one slice).
 template <typename T>
 hipError_t launch_backproject(const dect_plan* p, int ch, const BpArgs<T>& a, hipStream_t s);
+// Waves per workgroup that a transpose launch runs (values of `elem` bytes, `width` of them to
+// a record): the plan's choice, doubled (to at most 16) while the slice's blocks would leave a
+// compute unit fewer than 64 waves: at 256^2 (256 blocks) 4, 8 and 16 waves took 58, 38 and
+// 31 us, at 512^2 8 and 16 waves the same 107 us.  It hangs on the slice's blocks alone, so a
+// batch sums as its slices do.  Wide double-precision records keep to 8 (registers).  Choices
+// with the same result are one launch: the tuner times it once, batches share it.
+inline int bp_waves_for(size_t elem, int width, int waves, int blocks) {
+    const int most = elem == 8 && width > 4 ? 8 : 16;
+    while (waves < most && (long)blocks * waves < 256l * 64) waves *= 2;
+    return waves;
+}
 // ADMM epilogue variants of R^T on quad records, one or n slices; `waves` (2, 4
-// or 8) split the views of a workgroup.  sums64: keep the sums in double precision
+// or 8, or what they come to) split the views of a workgroup.  sums64: keep the sums in double precision
 // (the products of an FP32 plan are exact in double; the result is rounded once).
 template <typename T>
 hipError_t launch_backproject_admm(int sym, int waves, int epi, const BpArgs<T>* dev,
@@ -457,7 +468,7 @@ struct SliceJob {
     long N, M;
     int sym, bp_gx, bp_gy, pj_gx, pj_gy;
     int pj_rays;             // projector rays per lane
-    int bp_waves, pj_waves;  // workgroup shapes of the plan
+    int bp_waves, pj_waves;  // workgroup shapes of the plan (the transpose's as it runs)
     int pj_views, pj_chunk;  // projector lane layout and workgroup order of the plan
     int cg_iters, rho_mode;  // launch structure: slices share launches only if these agree
     int rt_sums64;           // the ADMM transposes sum in double (dect_rt_sums)

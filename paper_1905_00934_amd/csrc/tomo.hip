@@ -975,20 +975,9 @@ hipError_t bp_plain(const BpArgs<T>& one, T* quad, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Waves per workgroup of a transpose launch: the plan's choice, doubled (to at most 16) while
-// the slice's blocks would leave a compute unit fewer than 64 waves: at 256^2 (256 blocks)
-// 4, 8 and 16 waves took 58, 38 and 31 us, at 512^2 8 and 16 waves the same 107 us.  It hangs
-// on the slice's blocks alone, so a batch sums as its slices do.  Wide double-precision records keep to 8 (registers).
-template <typename T, int W>
-int bp_waves_for(int waves, int blocks) {
-    const int most = sizeof(T) == 8 && W > 4 ? 8 : 16;
-    while (waves < most && (long)blocks * waves < 256l * 64) waves *= 2;
-    return waves;
-}
-
 template <typename T, int CH, int SYM>
 hipError_t bp_plain_w(int waves, const BpArgs<T>& one, T* quad, hipStream_t s) {
-    switch (bp_waves_for<T, CH * SYM>(waves, one.gx * one.gy)) {
+    switch (bp_waves_for(sizeof(T), CH * SYM, waves, one.gx * one.gy)) {
         case 2: return bp_plain<T, CH, SYM, 2>(one, quad, s);
         case 4: return bp_plain<T, CH, SYM, 4>(one, quad, s);
         case 8: return bp_plain<T, CH, SYM, 8>(one, quad, s);
@@ -1028,7 +1017,7 @@ hipError_t bp_admm_t(int epi, const BpArgs<T>* dev, const BpArgs<T>& one, int n,
 template <typename T, int SYM, bool BATCH, typename A>
 hipError_t bp_admm_w(int waves, int epi, const BpArgs<T>* dev, const BpArgs<T>& one, int n, int gx,
                      int gy, hipStream_t s) {
-    switch (bp_waves_for<T, 2 * SYM>(waves, gx * gy)) {
+    switch (bp_waves_for(sizeof(T), 2 * SYM, waves, gx * gy)) {
         case 2: return bp_admm_t<T, SYM, BATCH, 2, A>(epi, dev, one, n, gx, gy, s);
         case 4: return bp_admm_t<T, SYM, BATCH, 4, A>(epi, dev, one, n, gx, gy, s);
         case 8: return bp_admm_t<T, SYM, BATCH, 8, A>(epi, dev, one, n, gx, gy, s);

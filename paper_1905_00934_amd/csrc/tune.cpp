@@ -5,7 +5,7 @@
 // Both kernels read every value they need whatever the shape; the shape changes
 // only how a workgroup's waves share the views (transpose) or the lines
 // (projector), i.e. the order in which partial sums are added.  Slices share
-// batched launches only when their plans' shapes agree.
+// batched launches only when the shapes that their plans run agree.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -117,7 +117,9 @@ dect_status time_candidates(dect_plan* p, hipStream_t s, dect_launch& out) {
     };
     Timing bp_def, bp_best;
     int bp_w = kBpDefault;
+    auto runs = [&](int w) { return bp_waves_for(p->elem, 2 * p->sym, w, bp_blocks(p)); };
     for (int w : kWaves) {
+        if (w != kBpDefault && runs(w) == runs(kBpDefault)) continue;  // the same launch
         Timing t;
         rc = timed([&] { return launch_backproject_admm<T>(J.sym, w, EPI_Q, nullptr, J.q, 1,
                                                            J.bp_gx, J.bp_gy, s); }, t);
