@@ -30,11 +30,13 @@ bool valid_waves(int w) { return w == 2 || w == 4 || w == 8; }
 bool valid_views(int v) { return v == 1 || v == 2 || v == 4 || v == 8; }
 bool valid_chunk(int c) { return c >= 1 && c <= 16; }
 
+// v3: the version of the kernels and of what a shape means to them.  Entries under another one
+// were timed on other kernels and are passed over; a change of either raises it.
 dect_status cache_key(const dect_plan* p, std::string& key) {
     hipDeviceProp_t prop;
     DECT_HIP(hipGetDeviceProperties(&prop, p->device));
     char buf[256];
-    std::snprintf(buf, sizeof buf, "v2:%s:%s:%s:%dx%d:%dx%d:sym%d", prop.gcnArchName,
+    std::snprintf(buf, sizeof buf, "v3:%s:%s:%s:%dx%d:%dx%d:sym%d", prop.gcnArchName,
                   p->dtype == DECT_F32 ? "f32" : "f64",
                   p->geom.kind == DECT_FAN ? "fan" : "parallel", p->nx, p->ny, p->V, p->D, p->sym);
     for (char* c = buf; *c; ++c)

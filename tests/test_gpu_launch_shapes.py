@@ -124,3 +124,13 @@ def test_admm_transposes_of_every_wave_count(name, waves):
     x = st.x.cpu().numpy()
     for b in range(2):
         assert np.linalg.norm(x[..., b] - ost.x[b]) <= 1e-8 * np.linalg.norm(ost.x[b])
+
+
+def test_cache_entries_of_earlier_kernels_are_not_used(tmp_path):
+    cache = tmp_path / "tune.txt"
+    plan = dect.Plan(SMALL, SPEC, F32)
+    assert plan.tune(str(cache))["from_cache"] == 0
+    assert plan.tune(str(cache))["from_cache"] == 1
+    fields = cache.read_text().split(":", 1)
+    cache.write_text("v2:" + fields[1])
+    assert plan.tune(str(cache))["from_cache"] == 0
