@@ -23,12 +23,15 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+# tomo.hip: its kernels' first two pointers (the projector's workgroup list is the second) are
+# in registers when a wave starts.
+FLAGS_FOR = {"tomo.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=4"]}
 
 
 def _compile(src: str, out_dir: str = OUT_DIR, defines=()) -> str:
     obj = os.path.join(out_dir, os.path.basename(src) + ".o")
     lang = ["-x", "hip"] if src.endswith(".cpp") else []
-    cmd = [HIPCC, *FLAGS, *[f"-D{d}" for d in defines], *lang, "-c",
+    cmd = [HIPCC, *FLAGS, *FLAGS_FOR.get(src, []), *[f"-D{d}" for d in defines], *lang, "-c",
            os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

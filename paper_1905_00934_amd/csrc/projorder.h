@@ -15,24 +15,34 @@ struct ViewSplit {
     int split, first;
 };
 
+// What a workgroup costs beside its lines, in lines: its start and end (a lone workgroup of a
+// 101^2 fan with 13 lines per wave takes 8 us, of which the lines are about a third).  16 left
+// the XCDs with few lines with many more workgroups than the others; 64, 512 and 4096 measured
+// within 2 % of this.
+constexpr long kProjStart = 128;
+
 // Workgroup list of the projector for one lane layout (64 / bv bins of nv views each): one
 // workgroup per tile and axis that any of its rays steps along (tiles at a view's 45 degree
-// bin have both; a workgroup serves the rays of one axis), in the XCD-aware order of
-// proj_tile, each XCD's sorted by the lines their rays cross, longest first.  In the plain
-// order with both axes of a tile in one workgroup, such a workgroup started last and ran
-// alone: at 512^2 the others ended at 60 us, the launch at 107.  Entry: 2 (bg gy + vg) +
-// axis, or -1 (none).
+// bin have both; a workgroup serves the rays of one axis), each XCD's in the order of the lines
+// their rays cross, longest first.  In the plain order with both axes of a tile in one
+// workgroup, such a workgroup started last and ran alone: at 512^2 the others ended at 60 us,
+// the launch at 107.  A tile goes to the XCD of the XCD-aware order (proj_tile) while that one
+// has less than its share and a sixteenth, else to the one with least: detectors of few bin
+// groups left XCDs idle (64^2 / 90 x 95 parallel ran on three of the eight: 10.1 us, now 9.5;
+// 100^2 / 140 x 149 in double precision 12.5 us, now 11.6); from about 384^2 on the order is
+// balanced as it is.  Entry: 2 (bg gy + vg) + axis, or -1 (none).
 inline std::vector<int> proj_launch_order(const dect_geometry& g, int Vb, const ViewSplit* splits,
                                           int bv, int nv, int chunk) {
     const int D = g.n_det;
     const int gx = proj_grid_x(D, bv), gy = proj_grid_y(Vb, nv), bb = 64 / bv;
     const unsigned blocks = proj_blocks(gx, gy, chunk);
     struct Tile {
-        int code, lines;
+        int code, lines, xcd;
     };
     std::vector<HostView> view(Vb);
     for (int v = 0; v < Vb; ++v) view[v] = host_view(g, v);
-    std::vector<Tile> by_xcd[kXcds];
+    std::vector<Tile> tiles;
+    long total = 0;
     for (unsigned id = 0; id < blocks; ++id) {
         int bg, vg;
         proj_tile(id, gy, chunk, bg, vg);
@@ -53,17 +63,29 @@ inline std::vector<int> proj_launch_order(const dect_geometry& g, int Vb, const 
             lines = std::max(lines, k1 - k0 + 1);
         }
         for (int ax = 0; ax < 2; ++ax)
-            if (axes >> ax & 1) by_xcd[id % kXcds].push_back({2 * (bg * gy + vg) + ax, lines});
+            if (axes >> ax & 1) {
+                tiles.push_back({2 * (bg * gy + vg) + ax, lines, (int)(id % kXcds)});
+                total += lines + kProjStart;
+            }
     }
+    std::stable_sort(tiles.begin(), tiles.end(),
+                     [](const Tile& a, const Tile& b) { return a.lines > b.lines; });
+    const long most = total / kXcds + total / (16 * kXcds) +
+                      (tiles.empty() ? 0 : tiles[0].lines + kProjStart);
+    std::vector<int> by_xcd[kXcds];
+    long load[kXcds] = {};
     size_t longest = 0;
-    for (auto& x : by_xcd) {
-        std::stable_sort(x.begin(), x.end(),
-                         [](const Tile& a, const Tile& b) { return a.lines > b.lines; });
-        longest = std::max(longest, x.size());
+    for (const Tile& t : tiles) {
+        int x = t.xcd;
+        if (load[x] + t.lines + kProjStart > most)
+            x = (int)(std::min_element(load, load + kXcds) - load);
+        load[x] += t.lines + kProjStart;
+        by_xcd[x].push_back(t.code);
+        longest = std::max(longest, by_xcd[x].size());
     }
     std::vector<int> order(longest * kXcds, -1);
     for (int x = 0; x < kXcds; ++x)
-        for (size_t n = 0; n < by_xcd[x].size(); ++n) order[n * kXcds + x] = by_xcd[x][n].code;
+        for (size_t n = 0; n < by_xcd[x].size(); ++n) order[n * kXcds + x] = by_xcd[x][n];
     return order;
 }
 
