@@ -122,14 +122,6 @@ DECT_HD inline void proj_tile(unsigned id, int gy, int chunk, int& bg, int& vg) 
     vg = within % gy;
 }
 
-// Sample k of a ray (phi0, slope) on a line of n_lines >= 2 pixels: Joseph's linear
-// interpolation at phi = phi0 + slope k between taps floor(phi) and floor(phi) + 1,
-// with the line extended by zeros.  Returned as two taps j0, j0 + 1 that always lie
-// inside the line (0 <= j0 <= n_lines - 2) and their weights w0, w1, each the tent
-// max(0, 1 - |phi - j|): 1 - alpha and alpha for an interior sample (alpha = phi -
-// floor(phi)), alpha on tap 0 when only floor(phi) + 1 = 0 is inside, 1 - alpha on tap
-// n_lines - 1 when only floor(phi) = n_lines - 1 is, and zero for a sample with no tap
-// inside.  So the loads need no bounds test.
 // The median of three values (no NaN): the hardware's three-operand median on the
 // device in single precision, the same selection elsewhere.
 template <typename T>
@@ -139,6 +131,17 @@ DECT_HD inline T med3(T a, T b, T c) {
 #endif
     return fmax(fmin(a, b), fmin(fmax(a, b), c));
 }
+
+// Sample k of a ray (phi0, slope) on a line of n_lines >= 2 pixels: Joseph's linear
+// interpolation at phi = phi0 + slope k between taps floor(phi) and floor(phi) + 1,
+// with the line extended by zeros.  Returned as two taps j0, j0 + 1 that always lie
+// inside the line (0 <= j0 <= n_lines - 2) and their weights w0, w1, each the tent
+// max(0, 1 - |phi - j|): 1 - alpha and alpha for an interior sample (alpha = phi -
+// floor(phi)), alpha on tap 0 when only floor(phi) + 1 = 0 is inside, 1 - alpha on tap
+// n_lines - 1 when only floor(phi) = n_lines - 1 is, and zero for a sample with no tap
+// inside.  So the loads need no bounds test.  The form of the samples that are read from the
+// image itself, and of a ray's sample range; staged samples take floor(phi) and floor(phi) + 1
+// of the zero-extended line as they are.
 template <typename T>
 DECT_HD inline int proj_taps(T phi0, T slope, T k, int n_lines, T& w0, T& w1) {
     const T ph = fma(slope, k, phi0);
@@ -149,12 +152,13 @@ DECT_HD inline int proj_taps(T phi0, T slope, T k, int n_lines, T& w0, T& w1) {
     return (int)j0;
 }
 
-// Staged image lines of the projector.  A wave whose rays all step along the same
-// axis reads, at sample k, line k of one orbit image; its 64 lanes stage the
-// kProjWin taps s(k) .. s(k) + kProjWin - 1 of that line into LDS (one each) and
-// read their two taps from there.  s(k) centres the window on the mean trajectory
-// of lanes 0 and 63 (the first bin of the first view and the last bin of the last:
-// the extreme rays of the wave), so that a wave's rays fall inside as long as they
+// Staged image lines of the projector.  The rays of a workgroup all step along the same
+// axis and read, at sample k, line k of one orbit image; a wave's 64 lanes stage the
+// kProjWin taps s(k) .. s(k) + kProjWin - 1 of that line into LDS (one each, zeros past the
+// line's ends) and read their two taps from there.  s(k) centres the window on the mean
+// trajectory of the extreme rays (the first ray of the first lane and the last ray of the last
+// lane that hold one: the first bin of the first view and the last bin of the last),
+// so that a wave's rays fall inside as long as they
 // spread over fewer than about kProjWin - 2 pixels of the line; a lane whose taps
 // are outside loads them directly.  The trajectory is held in fixed point with
 // kProjWinFrac fraction bits, so that the window start of each line is integer
@@ -165,8 +169,8 @@ constexpr int kProjWinFrac = 8;
 DECT_HD inline int proj_window(int A, int B, int k) {
     return ((A + B * k) >> kProjWinFrac) - (kProjWin / 2 - 1);
 }
-// The centre trajectory (A + B k) / 2^kProjWinFrac from the (phi0, slope) of lanes 0
-// and 63, clamped so that A + B k cannot overflow for k < 2^15.
+// The centre trajectory (A + B k) / 2^kProjWinFrac from the (phi0, slope) of the two extreme
+// rays, clamped so that A + B k cannot overflow for k < 2^15.
 template <typename T>
 DECT_HD inline void proj_window_line(T phi0_first, T slope_first, T phi0_last, T slope_last,
                                      int& A, int& B) {
@@ -175,6 +179,29 @@ DECT_HD inline void proj_window_line(T phi0_first, T slope_first, T phi0_last, T
     const T bc = fmin(fmax(T(0.5) * (slope_first + slope_last), T(-2)), T(2));
     A = (int)floor(ac * scale);
     B = (int)floor(bc * scale);
+}
+
+// The view and bin of ray r of a lane: R rays per lane, BV = 2^lbv views of 64 / BV bins each
+// to a wave.
+DECT_HD inline int proj_lane_view(int vg, int r, int R, int lbv, int lane) {
+    return ((vg * R + r) << lbv) + (lane & ((1 << lbv) - 1));
+}
+DECT_HD inline int proj_lane_bin(int bg, int lbv, int lane) {
+    return bg * (64 >> lbv) + (lane >> lbv);
+}
+
+// The loads of a staged line are checked against its end, not clamped: a buffer of
+// proj_line_bytes from part `part` of the line's first record on (records of `parts` parts of
+// `bytes` each), and lane's record at proj_line_offset of it.  A record past the end lies past
+// those bytes, and one before the start wraps to an offset of almost 2^32, far past them: a
+// window lies within 2^23 records of the start (proj_window's 32 bits less its fraction bits),
+// records take up to 128 bytes, and of longer lines the first 2^31 bytes are enough.
+DECT_HD inline unsigned proj_line_bytes(int n_lines, int parts, int part, unsigned bytes) {
+    const unsigned long n = ((unsigned long)n_lines * parts - part) * bytes;
+    return n < 0x80000000ul ? (unsigned)n : 0x80000000u;
+}
+DECT_HD inline unsigned proj_line_offset(int start, int lane, int parts, unsigned bytes) {
+    return (unsigned)(start + lane) * ((unsigned)parts * bytes);
 }
 
 // The samples k0..k1 of a ray (phi0, slope) with n_steps samples over n_lines image

@@ -291,7 +291,6 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
     const ProjArgs<T> A = pick_args<BATCH>(dev, one);
     const int nx = A.nx, ny = A.ny, Vb = A.Vb, D = A.D;
     const int BV = RPL * A.views, lbv = __builtin_ctz((unsigned)BV);
-    const int BB = 64 >> lbv;
     if (BATCH && (int)blockIdx.x >= A.blocks[RPL - 1]) return;  // beyond this slice
     // One slice's list is an argument of its own, in registers when the kernel starts: its entry
     // loads beside the other arguments, not after them (160^2 / 224 x 320, FP32, one channel:
@@ -308,7 +307,7 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
     T* __restrict__ sino = A.sino;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = bg * BB + (lane >> lbv);
+    const int b = proj_lane_bin(bg, lbv, lane);
     T phi0[RPL], slope[RPL], step[RPL];  // a ray of the other axis, or none: never inside
     bool on[RPL];
     // The lines the workgroup's rays cross: outside a ray's range both taps of every sample
@@ -321,7 +320,7 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
     T acc[RPL][W];
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-        const int v = (vg * RPL + r) * BV + (lane & (BV - 1));
+        const int v = proj_lane_view(vg, r, RPL, lbv, lane);
         const RayParam<T> q = rays[(size_t)(v < Vb ? v : Vb - 1) * D + (b < D ? b : D - 1)];
         on[r] = b < D && v < Vb && (q.pad == T(0)) == (ax == 0);
         any = any || on[r];
@@ -365,11 +364,11 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
                             lane_value(sb, last), wa, wb);
         wa = __builtin_amdgcn_readfirstlane(wa);
         wb = __builtin_amdgcn_readfirstlane(wb);
-        const int line_bytes = (wl * PARTS - part) * (int)sizeof(V);
+        const unsigned line_bytes = proj_line_bytes(wl, PARTS, part, sizeof(V));
         auto load_line = [&](int k, int start, VC (&o)[NCH]) {
             __amdgpu_buffer_rsrc_t line = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<V*>(img + (size_t)k * wl * PARTS), 0, line_bytes, 0x00027000);
-            const unsigned off = (unsigned)(start + lane) * (unsigned)(PARTS * sizeof(V));
+                const_cast<V*>(img + (size_t)k * wl * PARTS), 0, (int)line_bytes, 0x00027000);
+            const unsigned off = proj_line_offset(start, lane, PARTS, sizeof(V));
 #pragma unroll
             for (int h = 0; h < NCH; ++h) o[h] = line_load<VC>(line, off + h * sizeof(VC));
         };
@@ -462,7 +461,7 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
         for (int c = 0; c < W; ++c) s_win[wave][c / CE][lane].v[c % CE] = acc[r][c];
         __syncthreads();
         if (wave != r % KS || !on[r]) continue;
-        const int v = (vg * RPL + r) * BV + (lane & (BV - 1));
+        const int v = proj_lane_view(vg, r, RPL, lbv, lane);
         T sum[W];
 #pragma unroll
         for (int c = 0; c < W; ++c) sum[c] = s_win[0][c / CE][lane].v[c % CE];
