@@ -248,16 +248,17 @@ SliceJob<T> make_job(const dect_plan* p, const void* mh, const void* ml, const v
     J.M = p->M;
     J.sym = p->sym;
     J.bp_waves = bp_waves_for(sizeof(T), 2 * p->sym, p->bp_waves, bp_blocks(p));
+    const dect_plan::ProjOrder* shape = p->pj_shape;
     J.pj_waves = p->pj_waves;
-    J.pj_views = p->pj_views;
-    J.pj_chunk = p->pj_chunk;
-    J.pj_gx = proj_grid_x(p->D, p->pj_views);
-    J.pj_gy = proj_grid_y(p->Vb, p->pj_views);
-    J.pj_rays = proj_rays((int)sizeof(T) * 2 * p->sym, p->Vb, p->D, p->pj_views, p->pj_waves);
+    J.pj_views = shape->views;
+    J.pj_chunk = shape->chunk;
+    J.pj_gx = proj_grid_x(p->D, J.pj_views);
+    J.pj_gy = proj_grid_y(p->Vb, J.pj_views);
+    J.pj_rays = proj_rays((int)sizeof(T) * 2 * p->sym, p->Vb, p->D, J.pj_views, J.pj_waves);
     J.orb = OrbitArgs<T>{pp, pO, pOT, p->nx, p->ny};
     J.prj = ProjArgs<T>{static_cast<const RayParam<T>*>(p->rays), pO, pOT, Rp, p->nx, p->ny,
-                        p->Vb, p->D, p->pj_views, {p->pj_order[0], p->pj_order[1]},
-                        {p->pj_blocks[0], p->pj_blocks[1]}, 0};
+                        p->Vb, p->D};
+    proj_take_shape(J.prj, *shape);
     // Right-hand side of Eq. (12) and the initial CG residual.
     BpArgs<T> b{};
     fill_bp_plan<T>(p, b);

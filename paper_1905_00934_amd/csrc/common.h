@@ -3,8 +3,11 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
+#include <list>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -93,23 +96,22 @@ struct dect_plan {
     // Rotational symmetry order (4: views v + k V/4 are quarter turns of base
     // view v; 1: none) and the number of base views Vb = V / sym.
     int sym = 1, Vb = 0;
-    // Workgroup shapes of the ADMM transpose (waves splitting the views) and
-    // projector (waves splitting the lines): 2, 4 or 8, set by dect_plan_tune.
-    int bp_waves = 4, pj_waves = 8;
-    // Projector lane layout (base views per wave) and XCD chunk (bin groups per XCD
-    // turn), also set by dect_plan_tune.
-    int pj_views = 2, pj_chunk = 1;
+    // Workgroup shapes of the ADMM transpose (waves splitting the views) and projector (waves
+    // splitting the lines): 2, 4 or 8, set by dect_plan_set_launch and dect_plan_tune.
+    std::atomic<int> bp_waves{4}, pj_waves{8};
     std::vector<dect::ViewSplit> splits;  // per base view, the bins of each ray axis
-    // Workgroup lists of the projector for the launch shapes used so far, kept (never
-    // rewritten) until the plan goes, by rays per lane - 1 (proj_order_for).
+    // A projector lane layout (base views per wave) and XCD chunk (bin groups per XCD turn) with
+    // its workgroup lists, by rays per lane - 1 (proj_order_for).  Those used so far are kept,
+    // unchanged, until the plan goes.  The current one is read as a whole, so that a launch
+    // beside a change of shape never runs one shape on the list of another.
     struct ProjOrder {
         int views, chunk;
         int* order[2];
         int blocks[2];
     };
-    std::vector<ProjOrder> pj_orders;
-    const int* pj_order[2] = {nullptr, nullptr};  // of the current shape
-    int pj_blocks[2] = {0, 0};
+    std::mutex pj_mu;  // guards pj_orders
+    std::list<ProjOrder> pj_orders;
+    std::atomic<const ProjOrder*> pj_shape{nullptr};
     // device tables
     void* rays = nullptr;   // RayParam<T>[Vb * D]
     void* views = nullptr;  // ViewParam<T>[Vb]
@@ -170,10 +172,14 @@ namespace dect {
 // Workgroups of the transposed projector (8x8 pixel orbits each).
 int bp_blocks(const dect_plan* p);
 
-// The projector's workgroup lists for a lane layout and chunk (device tables) and their
-// lengths, built on first use.
-dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&order)[2],
-                           int (&blocks)[2]);
+// The projector's workgroup lists for a lane layout and chunk (device tables), built on first
+// use.
+dect_status proj_order_for(dect_plan* p, int views, int chunk, const dect_plan::ProjOrder** out);
+
+// Launch shapes that a plan takes (dect_launch).
+inline bool launch_waves_ok(int w) { return w == 2 || w == 4 || w == 8; }
+inline bool launch_views_ok(int v) { return v == 1 || v == 2 || v == 4 || v == 8; }
+inline bool launch_chunk_ok(int c) { return c >= 1 && c <= 16; }
 
 // Column i and row j of pixel pix of an image nx wide; images hold fewer than 2^30
 // pixels, so the division is unsigned 32-bit.

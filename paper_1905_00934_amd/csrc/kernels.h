@@ -88,6 +88,16 @@ struct ProjArgs {
     int grid;             // workgroups of the launch if more: a batch's longest list
 };
 
+// The launch shape's part of the arguments.
+template <typename T>
+inline void proj_take_shape(ProjArgs<T>& a, const dect_plan::ProjOrder& shape) {
+    a.views = shape.views;
+    for (int r = 0; r < 2; ++r) {
+        a.order[r] = shape.order[r];
+        a.blocks[r] = shape.blocks[r];
+    }
+}
+
 // Fixed-order reductions of block partials and the scalar updates (one block per
 // slice, or the last workgroup of a transpose).  scal == nullptr marks an empty slot.
 enum RedMode : int { RED_NONE = 0, RED_ALPHA = 1, RED_BETA = 2, RED_FINAL = 3 };

@@ -424,38 +424,35 @@ void make_layout(dect_plan* p) {
 
 // Kept per shape, at most 64 of them.  A shape may be chosen while a stream is captured (the
 // copy then runs on a stream of its own, outside the capture) or another device is current.
-dect_status proj_order_for(dect_plan* p, int views, int chunk, const int* (&order)[2],
-                           int (&blocks)[2]) {
-    const dect_plan::ProjOrder* hit = nullptr;
+dect_status proj_order_for(dect_plan* p, int views, int chunk, const dect_plan::ProjOrder** out) {
+    std::lock_guard<std::mutex> lk(p->pj_mu);
     for (const auto& o : p->pj_orders)
-        if (o.views == views && o.chunk == chunk) hit = &o;
-    if (!hit) {
-        dect_plan::ProjOrder o{views, chunk, {nullptr, nullptr}, {0, 0}};
-        dect_status st = DECT_OK;
-        try {
-            p->pj_orders.reserve(p->pj_orders.size() + 1);
-            for (int R = 1; R <= 2 && R * views <= 64 && st == DECT_OK; ++R) {
-                const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
-                                                             R * views, R * R * views, chunk);
-                st = upload_aside(p->device, t.data(), t.size() * sizeof(int),
-                                  reinterpret_cast<void**>(&o.order[R - 1]));
-                o.blocks[R - 1] = (int)t.size();
-            }
-        } catch (const std::bad_alloc&) {
-            st = fail(DECT_E_NOMEM, "host allocation failed");
+        if (o.views == views && o.chunk == chunk) {
+            *out = &o;
+            return DECT_OK;
         }
-        if (st != DECT_OK) {
-            (void)hipFree(o.order[0]);
-            (void)hipFree(o.order[1]);
-            return st;
+    std::list<dect_plan::ProjOrder> made;
+    dect_status st = DECT_OK;
+    try {
+        made.push_back({views, chunk, {nullptr, nullptr}, {0, 0}});
+        dect_plan::ProjOrder& o = made.back();
+        for (int R = 1; R <= 2 && R * views <= 64 && st == DECT_OK; ++R) {
+            const std::vector<int> t = proj_launch_order(p->geom, p->Vb, p->splits.data(),
+                                                         R * views, R * R * views, chunk);
+            st = upload_aside(p->device, t.data(), t.size() * sizeof(int),
+                              reinterpret_cast<void**>(&o.order[R - 1]));
+            o.blocks[R - 1] = (int)t.size();
         }
-        p->pj_orders.push_back(o);  // reserved above
-        hit = &p->pj_orders.back();
+    } catch (const std::bad_alloc&) {
+        st = fail(DECT_E_NOMEM, "host allocation failed");
     }
-    for (int r = 0; r < 2; ++r) {
-        order[r] = hit->order[r];
-        blocks[r] = hit->blocks[r];
+    if (st != DECT_OK) {
+        for (const auto& o : made)
+            for (int* q : o.order) (void)hipFree(q);
+        return st;
     }
+    p->pj_orders.splice(p->pj_orders.end(), made);
+    *out = &p->pj_orders.back();
     return DECT_OK;
 }
 
@@ -537,8 +534,10 @@ dect_status dect_plan_create(const dect_geometry* geom, const dect_spectra* spec
     try {
         st = dtype == DECT_F32 ? build_tables<float>(p, spec) : build_tables<double>(p, spec);
         if (st == DECT_OK) st = build_block_order(p);
+        const dect_plan::ProjOrder* shape = nullptr;
         if (st == DECT_OK)
-            st = proj_order_for(p, p->pj_views, p->pj_chunk, p->pj_order, p->pj_blocks);
+            st = proj_order_for(p, kProjViewsDefault, kProjChunkDefault, &shape);
+        p->pj_shape = shape;
         if (st == DECT_OK)
             st = dtype == DECT_F32 ? build_precond<float>(p) : build_precond<double>(p);
         if (st == DECT_OK) st = dtype == DECT_F32 ? build_fbp<float>(p) : build_fbp<double>(p);
@@ -607,6 +606,35 @@ dect_status dect_plan_get_info(const dect_plan* p, dect_plan_info* out) {
             }
         }
     *out = info;
+    return DECT_OK;
+}
+
+dect_status dect_plan_set_launch(dect_plan* p, int bp_waves, int proj_waves, int proj_views,
+                                 int proj_chunk) {
+    if (!p) return fail(DECT_E_ARG, "null plan");
+    if (!launch_waves_ok(bp_waves) || !launch_waves_ok(proj_waves))
+        return fail(DECT_E_ARG, "waves per workgroup must be 2, 4 or 8 (got %d, %d)", bp_waves,
+                    proj_waves);
+    if (!launch_views_ok(proj_views) || !launch_chunk_ok(proj_chunk))
+        return fail(DECT_E_ARG, "projector views per wave must be 1, 2, 4 or 8 and the chunk "
+                                "1 to 16 (got %d, %d)", proj_views, proj_chunk);
+    const dect_plan::ProjOrder* shape = nullptr;
+    const dect_status st = proj_order_for(p, proj_views, proj_chunk, &shape);
+    if (st) return st;
+    p->bp_waves = bp_waves;
+    p->pj_waves = proj_waves;
+    p->pj_shape = shape;
+    return DECT_OK;
+}
+
+dect_status dect_plan_get_launch(const dect_plan* p, dect_launch* out) {
+    if (!p || !out) return fail(DECT_E_ARG, "null argument");
+    std::memset(out, 0, sizeof *out);
+    const dect_plan::ProjOrder* shape = p->pj_shape;
+    out->bp_waves = p->bp_waves;
+    out->proj_waves = p->pj_waves;
+    out->proj_views = shape->views;
+    out->proj_chunk = shape->chunk;
     return DECT_OK;
 }
 

@@ -1093,8 +1093,8 @@ hipError_t launch_project_with(const dect_plan* p, const void* img, void* sino, 
     T* OT = static_cast<T*>(OT_);
     OrbitArgs<T> o{static_cast<const T*>(img), O, OT, p->nx, p->ny};
     ProjArgs<T> q{static_cast<const RayParam<T>*>(p->rays), O, OT, static_cast<T*>(sino), p->nx,
-                  p->ny, p->Vb, p->D, p->pj_views, {p->pj_order[0], p->pj_order[1]},
-                  {p->pj_blocks[0], p->pj_blocks[1]}, 0};
+                  p->ny, p->Vb, p->D};
+    proj_take_shape(q, *p->pj_shape.load());
     if (p->sym == 4) {
         switch (ch) {
             case 1: return project_t<T, 1, 4, false, kLineSplit>(nullptr, o, nullptr, q, 1, p->N, s);

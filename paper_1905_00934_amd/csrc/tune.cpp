@@ -26,10 +26,6 @@ constexpr int kBpDefault = 4, kPjDefault = 8;
 // median batch average, its spread (max - min) / min over the batches.
 constexpr int kBatches = 3, kReps = 8;
 
-bool valid_waves(int w) { return w == 2 || w == 4 || w == 8; }
-bool valid_views(int v) { return v == 1 || v == 2 || v == 4 || v == 8; }
-bool valid_chunk(int c) { return c >= 1 && c <= 16; }
-
 // v3: the version of the kernels and of what a shape means to them.  Entries under another one
 // were timed on other kernels and are passed over; a change of either raises it.
 dect_status cache_key(const dect_plan* p, std::string& key) {
@@ -56,8 +52,8 @@ bool cache_lookup(const char* path, const std::string& key, dect_launch& out) {
         if (line[0] == '#') continue;
         if (std::sscanf(line, "%299s %d %d %d %d %lf %lf", k, &e.bp_waves, &e.proj_waves,
                         &e.proj_views, &e.proj_chunk, &e.bp_us, &e.proj_us) == 7 &&
-            key == k && valid_waves(e.bp_waves) && valid_waves(e.proj_waves) &&
-            valid_views(e.proj_views) && valid_chunk(e.proj_chunk)) {
+            key == k && launch_waves_ok(e.bp_waves) && launch_waves_ok(e.proj_waves) &&
+            launch_views_ok(e.proj_views) && launch_chunk_ok(e.proj_chunk)) {
             out = e;
             found = true;
         }
@@ -142,9 +138,10 @@ dect_status time_candidates(dect_plan* p, hipStream_t s, dect_launch& out) {
         for (int v : kViews)
             for (int c : kChunks) {
                 ProjArgs<T> a = J.prj;
-                a.views = v;
-                rc = proj_order_for(p, v, c, a.order, a.blocks);
+                const dect_plan::ProjOrder* shape = nullptr;
+                rc = proj_order_for(p, v, c, &shape);
                 if (rc) return done(rc);
+                proj_take_shape(a, *shape);
                 Timing t;
                 rc = timed([&] { return launch_project_pair<T>(J.sym, w, nullptr, J.orb, nullptr, a,
                                                                1, J.N, s); }, t);
@@ -182,34 +179,6 @@ using namespace dect;
 
 extern "C" {
 
-dect_status dect_plan_set_launch(dect_plan* p, int bp_waves, int proj_waves, int proj_views,
-                                 int proj_chunk) {
-    if (!p) return fail(DECT_E_ARG, "null plan");
-    if (!valid_waves(bp_waves) || !valid_waves(proj_waves))
-        return fail(DECT_E_ARG, "waves per workgroup must be 2, 4 or 8 (got %d, %d)", bp_waves,
-                    proj_waves);
-    if (!valid_views(proj_views) || !valid_chunk(proj_chunk))
-        return fail(DECT_E_ARG, "projector views per wave must be 1, 2, 4 or 8 and the chunk "
-                                "1 to 16 (got %d, %d)", proj_views, proj_chunk);
-    const dect_status st = proj_order_for(p, proj_views, proj_chunk, p->pj_order, p->pj_blocks);
-    if (st) return st;
-    p->bp_waves = bp_waves;
-    p->pj_waves = proj_waves;
-    p->pj_views = proj_views;
-    p->pj_chunk = proj_chunk;
-    return DECT_OK;
-}
-
-dect_status dect_plan_get_launch(const dect_plan* p, dect_launch* out) {
-    if (!p || !out) return fail(DECT_E_ARG, "null argument");
-    std::memset(out, 0, sizeof *out);
-    out->bp_waves = p->bp_waves;
-    out->proj_waves = p->pj_waves;
-    out->proj_views = p->pj_views;
-    out->proj_chunk = p->pj_chunk;
-    return DECT_OK;
-}
-
 dect_status dect_plan_tune(dect_plan* p, const char* cache_path, int flags, dect_launch* out,
                            void* stream) {
     if (!p) return fail(DECT_E_ARG, "null plan");
@@ -233,13 +202,8 @@ dect_status dect_plan_tune(dect_plan* p, const char* cache_path, int flags, dect
             std::fclose(f);
         }
     }
-    const dect_status ost = proj_order_for(p, best.proj_views, best.proj_chunk, p->pj_order,
-                                           p->pj_blocks);
-    if (ost) return ost;
-    p->bp_waves = best.bp_waves;
-    p->pj_waves = best.proj_waves;
-    p->pj_views = best.proj_views;
-    p->pj_chunk = best.proj_chunk;
+    rc = dect_plan_set_launch(p, best.bp_waves, best.proj_waves, best.proj_views, best.proj_chunk);
+    if (rc) return rc;
     if (out) *out = best;
     return DECT_OK;
 }

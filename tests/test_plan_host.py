@@ -1,5 +1,6 @@
 """The plan's host code over a HIP runtime that lives on the host (tests/plan_host.cpp): which
-device its lists are put on, and what a shortage of host memory does."""
+device its lists are put on, what a shortage of host memory does, and shapes chosen by several
+threads."""
 import os
 import shutil
 import subprocess
@@ -16,7 +17,7 @@ def program(tmp_path_factory):
     if shutil.which("g++") is None or not os.path.isdir(os.path.join(rocm, "include", "hip")):
         pytest.skip("g++ or the HIP headers are not available")
     exe = str(tmp_path_factory.mktemp("ph") / "plan_host")
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__",
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-pthread", "-D__HIP_PLATFORM_AMD__",
            "-I", os.path.join(rocm, "include"), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            os.path.join(ROOT, "tests", "plan_host.cpp"), os.path.join(CSRC, "plan.cpp"),
            "-o", exe]
@@ -36,3 +37,7 @@ def test_projector_lists_are_on_the_plans_device(program):
 
 def test_projector_lists_without_host_memory(program):
     _run(program, "nomem")
+
+
+def test_launch_shapes_chosen_by_several_threads(program):
+    _run(program, "threads")
