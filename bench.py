@@ -27,7 +27,8 @@ HBM_PEAK_GBS = 8000.0
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "admm_fan512_hbm_traffic.txt")
 KERNEL_SOURCES = ["tomo.hip", "udm.hip", "admm.hip", "kernels.h", "common.h", "epilogue.h", "tv.h",
-                  "reduce.h", "projidx.h", "bpidx.h"]
+                  "reduce.h", "projidx.h", "projorder.h", "bpidx.h", "plan.cpp", "fft.hip",
+                  "fftcore.h"]
 
 
 def kernel_source_hash() -> str:
