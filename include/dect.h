@@ -379,8 +379,8 @@ typedef struct {
  * device, precision and problem shape, else by timing every candidate on a scratch
  * state on `stream` (synchronises; allocates a temporary state) and appending the
  * result to the cache (cache_path NULL: no cache).  Candidates: bp_waves 2, 4, 8 for
- * the transpose, of those that run the same launch one; proj_waves 2, 4, 8 x proj_views 1, 2, 4 x proj_chunk 1, 2, 4 for the
- * projector; each timed as the median of 3 batches of 8 launches after 2 warm-up
+ * the transpose, of those that run the same launch one; proj_waves 2, 4, 8 x
+ * proj_views 1, 2, 4 x proj_chunk 1, 2, 4 for the projector; each timed as the median of 3 batches of 8 launches after 2 warm-up
  * launches.  A candidate replaces the default only if it is faster by more than the
  * larger of 1 % and the batches' spread, so run-to-run noise does not change the
  * shapes.  The plan is updated; out (may be NULL) receives the choice. */

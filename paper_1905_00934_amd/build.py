@@ -12,7 +12,6 @@ OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "libdect.so")
 SOURCES = ["plan.cpp", "profile.cpp", "tomo.hip", "udm.hip", "admm.hip", "batch.cpp",
            "server.cpp", "tune.cpp", "fft.hip", "fbp.hip", "lmcg.hip"]
-HEADERS = ["bpidx.h", "common.h", "fftcore.h", "kernels.h", "profile.h", "projidx.h", "projorder.h", "runner.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -47,10 +47,9 @@ struct alignas(sizeof(T) * N) vec {
 // Joseph parameters of one ray.  An x-stepped ray (|d_x| >= |d_y|) is sampled at
 // every pixel column i at the fractional row phi(i) = phi0 + slope * i; a
 // y-stepped ray at every row j at the fractional column phi0 + slope * j.  Each
-// sample is weighted by `step`, the ray length between two samples.  The forward
-// projector and the plain transposed gather both evaluate phi with one fma on these
-// values; the weights they then form differ only by rounding (the projector
-// interpolates a0 + alpha (a1 - a0) and scales by step at the end).
+// sample is weighted by `step`, the ray length between two samples.  The projector
+// evaluates phi with one fma on these values, weighs the two taps by 1 - alpha and alpha
+// and scales by step at the end; the transpose forms the same weights from BpRay.
 template <typename T>
 struct alignas(sizeof(T) * 4) RayParam {
     T phi0, slope, step, pad;
@@ -115,8 +114,10 @@ struct dect_plan {
     // device tables
     void* rays = nullptr;   // RayParam<T>[Vb * D]
     void* views = nullptr;  // ViewParam<T>[Vb]
-    int* bp_order = nullptr;  // [bp_blocks]: the transpose's blocks in launch order (bp_block_order)
-    void* bp_rays = nullptr;  // BpRay<T>[Vb][D + 1]: the transpose's form of the rays, a zero record at each row's end
+    // [bp_blocks]: the transpose's blocks in launch order (build_block_order)
+    int* bp_order = nullptr;
+    // BpRay<T>[Vb][D + 1]: the transpose's form of the rays, a zero record at each row's end
+    void* bp_rays = nullptr;
     void* spec = nullptr;   // T[6 * Kmax]: lw_h, kc_h, kp_h, lw_l, kc_l, kp_l
     int kh = 0, kl = 0, kmax = 0;
     // Both spectra on one energy grid, for evaluating them with one exponential per

@@ -88,7 +88,8 @@ constexpr float kFbpFar = 16384.0f;    // bins of its pixels are then good to ha
 // Vb sees rot_(a+k)(p), so each bin and weight serves four views (k) and goes into four
 // pixels' sums; views an even and an odd number of turns on each take the bin and weight that
 // they would round to by themselves (two forms of one sum: bins differ by 1e-4 between them,
-// which is what single precision can tell).  The next window's loads are in flight while one is used.
+// which is what single precision can tell).  The next window's loads are in flight while one is
+// used.
 //
 // Per pixel and view: 11 vector instructions on a symmetric plan (37 where every pixel read
 // its two taps from memory behind four comparisons, one thread per pixel walking all views)
@@ -162,7 +163,8 @@ __global__ __launch_bounds__(64 * VS) void k_fbp_back(const T* __restrict__ Q, i
         }
         R nxt[SYM];
         auto fetch = [&](int n) __attribute__((always_inline)) {  // window n of the table
-            const int f = __builtin_amdgcn_readlane(first, n), m = __builtin_amdgcn_readlane(count, n);
+            const int f = __builtin_amdgcn_readlane(first, n);
+            const int m = __builtin_amdgcn_readlane(count, n);
             const int k = min(max(f + min(lane, m), -2), D) + 2;  // lanes past it: one address
             const R* q = rec + (size_t)(vc + n / SYM) * (D + 3);
 #pragma unroll

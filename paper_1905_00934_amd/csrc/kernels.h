@@ -293,8 +293,9 @@ template <typename T>
 hipError_t launch_project(const dect_plan* p, const void* img, void* sino, int ch, hipStream_t s);
 // Two-channel projection of the ADMM direction into quad-interleaved records, for
 // one slice (dev == nullptr: `one`) or n slices of its shape (dev: device arrays); `waves`
-// (2, 4 or 8) waves per workgroup split the lines, `pixels` orbit-image threads per slice.  orbit = false: the orbit images are
-// already in place (written by launch_rhs_orbit) and only the projector runs.
+// (2, 4 or 8) waves per workgroup split the lines, `pixels` orbit-image threads per slice.
+// orbit = false: the orbit images are already in place (written by launch_rhs_orbit) and only
+// the projector runs.
 template <typename T>
 hipError_t launch_project_pair(int sym, int waves, const OrbitArgs<T>* odev,
                                const OrbitArgs<T>& oone, const ProjArgs<T>* pdev,
@@ -325,8 +326,9 @@ inline int bp_waves_for(size_t elem, int width, int waves, int blocks) {
     return waves;
 }
 // ADMM epilogue variants of R^T on quad records, one or n slices; `waves` (2, 4
-// or 8, or what they come to) split the views of a workgroup.  sums64: keep the sums in double precision
-// (the products of an FP32 plan are exact in double; the result is rounded once).
+// or 8, or what they come to) split the views of a workgroup.  sums64: keep the sums in
+// double precision (the products of an FP32 plan are exact in double; the result is rounded
+// once).
 template <typename T>
 hipError_t launch_backproject_admm(int sym, int waves, int epi, const BpArgs<T>* dev,
                                    const BpArgs<T>& one, int n, int gx, int gy, hipStream_t s,

@@ -264,8 +264,8 @@ std::vector<int> bit_reversed(int lg) {
 }
 
 // Preconditioner of the x-update: the floored ramp max(|w|, 1/max(Py, Px)) on the
-// zero-padded DFT grid (|w| in cycles per pixel), bit-reversed in both axes, and the DFT twiddle factors
-// exp(-2 pi i k / P), k < P / 2, of both padded sides.
+// zero-padded DFT grid (|w| in cycles per pixel), bit-reversed in both axes, and the DFT
+// twiddle factors exp(-2 pi i k / P), k < P / 2, of both padded sides.
 template <typename T>
 dect_status build_precond(dect_plan* p) {
     p->px = pad_pow2(p->nx, p->lpx);

@@ -17,11 +17,12 @@
 // Transpose: one lane owns the rotation orbit of a pixel.  For every base view
 // and every orbit member it locates the bins whose samples can touch the pixel and
 // re-evaluates each candidate's interpolation weight from the same ray geometry;
-// each weight serves SYM (pixel, view) pairs.  The projector interpolates between a
-// sample's two taps by the fraction of its position and scales by the step length at the end, while the transpose forms each weight step max(0, 1 - |d|) from the
-// signed distance d of its own ray records, so the pair is a transpose up to rounding
-// (FP64 adjointness to 1e-12), not bit for bit.  The views are split over the waves
-// of a workgroup and the wave sums are added in a fixed order through LDS.
+// each weight serves SYM (pixel, view) pairs.  The projector weighs a sample's two taps by the
+// fraction of its position and scales by the step length at the end, while the transpose forms
+// each weight step max(0, 1 - |d|) from the signed distance d of its own ray records, so the
+// pair is a transpose up to rounding (FP64 adjointness to 1e-12), not bit for bit.  The views
+// are split over the waves of a workgroup and the wave sums are added in a fixed order through
+// LDS.
 #include <mutex>
 
 #include "bpidx.h"
@@ -479,7 +480,8 @@ __global__ __launch_bounds__(64 * KS) void k_project(const ProjArgs<T>* __restri
                 vec<T, CH> out;
 #pragma unroll
                 for (int c = 0; c < CH; ++c) out.v[c] = sum[s * CH + c] * step[r];
-                reinterpret_cast<vec<T, CH>*>(sino)[(size_t)(v + (part * SP + s) * Vb) * D + b] = out;
+                const int vs = v + (part * SP + s) * Vb;
+                reinterpret_cast<vec<T, CH>*>(sino)[(size_t)vs * D + b] = out;
             }
         }
     }
@@ -498,8 +500,8 @@ __device__ inline float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(
 // v + k' Vb, for all k'.
 //
 // Candidates of a pixel are the bins within h of its detector coordinate beta, h the largest
-// change of beta over one pixel along an axis (a ray more than one pixel step away along its minor axis has
-// no tap on the pixel); the weight max(0, step (1 - |d|)) of a candidate, d its signed
+// change of beta over one pixel along an axis (a ray more than one pixel step away along its
+// minor axis has no tap on the pixel); the weight max(0, step (1 - |d|)) of a candidate, d its signed
 // minor-axis distance, is the projector's linear-interpolation weight.
 //
 // Per view and member ("slot") the block's candidates lie in a window of kBpWin bins.
@@ -950,7 +952,8 @@ hipError_t project_t(const OrbitArgs<T>* odev, const OrbitArgs<T>& oone,
 
 // A standard [V][D][CH] sinogram as quad records [Vb][D][4][CH] (view v + k Vb is
 // rotation k of base view v), times the ray weights if there are any, the layout the
-// transpose of a quarter-turn symmetric plan reads: one record per thread, the four views' rows read and the records written along b.
+// transpose of a quarter-turn symmetric plan reads: one record per thread, the four views' rows
+// read and the records written along b.
 template <typename T, int CH>
 __global__ __launch_bounds__(256) void k_quad_records(const T* __restrict__ sino,
                                                       const T* __restrict__ weight, int Vb, int D,

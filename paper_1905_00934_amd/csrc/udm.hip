@@ -306,8 +306,9 @@ struct EvalPack {
 // lm_solve together.  Without a joint table (a weight below 2^-24 of its spectrum) the
 // spectra are evaluated apart.
 //
-// NT > 1 (with JT; the workgroup's rays): a ray whose iteration has the trial point and shift of its last evaluation
-// takes that evaluation's result, which would come out the same bit for bit.  This is what
+// NT > 1 (with JT; the workgroup's rays): a ray whose iteration has the trial point and shift
+// of its last evaluation takes that evaluation's result, which would come out the same bit for
+// bit.  This is what
 // most iterations of a converged ray are: its step is a few units of the point's last place
 // and rejected, and the growing damping leaves point and shift as they were (over 20
 // constrained iterations of a 512^2 slice, FP32, 61 % of the evaluations; 15 % of 10
@@ -324,8 +325,8 @@ struct EvalPack {
 // accepted: bit k set when LM iteration k (k < 32) accepted its trial point.
 template <typename T, bool CONSTR, bool JT, int NT>
 __device__ inline void lm_solve(EvalPack<T, NT>* pack, const T* __restrict__ spec, int kmax,
-                                int kh, int kl, const JointTab<T>& jt, T mh, T ml, T wh, T wl, T vc, T vp,
-                                T rc, T rp, int iters, T mu, StepBound sb, Point<T>& P,
+                                int kh, int kl, const JointTab<T>& jt, T mh, T ml, T wh, T wl,
+                                T vc, T vp, T rc, T rp, int iters, T mu, StepBound sb, Point<T>& P,
                                 unsigned& accepted) {
     constexpr T log2e = T(1.4426950408889634);
     constexpr bool PACK = NT > 1;
@@ -713,8 +714,8 @@ hipError_t launch_udm(const dect_plan* p, int mode, const UdmArgs<T>& a0, hipStr
     if (jt && mode == 3 && a.iters >= 4 && a.M >= 131072) {
         auto packed = [&](auto nt) {
             constexpr int NT = decltype(nt)::value;
-            hipLaunchKernelGGL((k_udm<T, 3, false, true, NT>), dim3((unsigned)((a.M + NT - 1) / NT)),
-                               dim3(NT), 0, s, nullptr, a);
+            const dim3 groups((unsigned)((a.M + NT - 1) / NT));
+            hipLaunchKernelGGL((k_udm<T, 3, false, true, NT>), groups, dim3(NT), 0, s, nullptr, a);
         };
         if (sizeof(T) == 4 && a.M >= 262144) packed(std::integral_constant<int, 512>{});
         else packed(std::integral_constant<int, 256>{});
