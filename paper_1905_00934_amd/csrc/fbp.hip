@@ -27,8 +27,8 @@ struct IntervalOf {  // (q[k], q[k + 1] - q[k]), CH values each
 template <typename T, int CH>
 using Interval = typename IntervalOf<T, CH>::type;
 
-// The row's FFT, filter and inverse in registers and LDS (fftcore.h).  10 us for 720 rows of 2048
-// points, FP32 (33 us with radix-2 passes on reordered rows); the chain of seven passes and
+// The row's FFT, filter and inverse in registers and LDS (fftcore.h).  13-15 us for 720 rows of
+// 2048 points, FP32 (33 us with radix-2 passes on reordered rows); the chain of seven passes and
 // their barriers bounds it, with 2.8 blocks per compute unit.
 // One view per block, two channels as one complex row.
 template <typename T, int CH>

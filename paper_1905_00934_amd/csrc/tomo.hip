@@ -264,9 +264,10 @@ __device__ inline U line_load(__amdgpu_buffer_rsrc_t line, unsigned off) {
 // weights are those of plain linear interpolation.  LDS takes 13.8 cycles for the write of a
 // 16-byte piece by a wave and 4.6 for a read (measured), so a record's two writes cost more
 // than a ray's four reads: RPL = 2 halves the writes, loads and loop overhead per ray.
-// Measured at 512^2 / 720 x 1024, FP32, two channels: 78 us against 101 us
-// with one ray per lane and workgroups of both axes; 350 views of 512 bins, parallel, one
-// channel: 36 us against 61.  What bounds it now is LDS (38 % of the waves' time waits for it).
+// Measured at 512^2 / 720 x 1024, FP32, two channels: 77 us against 94-101 us
+// with one ray per lane and workgroups of both axes; 350 x 301 pixels, 451 x 481 parallel rays,
+// one channel: 34 us against 58.  What bounds it now is LDS (50 % of its cycles active) and
+// VALU issue (69 %).
 //
 // Records of 128 bytes (four FP64 channels, quarter-turn symmetric) go in two halves of two
 // rotations, a workgroup each (blockIdx.y): 512^2 598 us, 256^2 91 us against 805 and 137
@@ -530,9 +531,9 @@ __device__ inline float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(
 // 512^2 / 720 x 1024 (two channels, FP32) 204 VALU instructions (341 with a footprint per
 // pixel, which took 62.9 M per launch against 37.2 M) and 46 LDS instructions of which the
 // 34 candidate reads take 4.6 cycles each and the 6 staging writes 13.8 (measured alone).
-// A launch takes 106-108 us (118-122 us before, at 4 waves per workgroup, 110-114 at 8);
-// 31 us at 256^2 (58 and 38); a plain one-channel transpose of 350 x 301 pixels over 451 x 481
-// parallel rays 47 us (97).
+// A launch takes 102-111 us (118-122 us before, at 4 waves per workgroup, 110-114 at 8);
+// 27 us at 256^2 (58 and 38); a plain one-channel transpose of 350 x 301 pixels over 451 x 481
+// parallel rays 46 us (97).
 constexpr int kBpSlots = 2;
 constexpr int kBpBatch = 64;
 
@@ -808,8 +809,11 @@ __device__ inline void gather_windows(const BpArgs<T>& a, int wave, int lane, in
 // only the sums round); the finished values are rounded to T once.
 //
 // Waves per SIMD that the registers are held to (the second launch bound).  The staged gather
-// waits on LDS, so it wants as many waves as its registers allow; what is spilled for them is
-// the batch's set-up and the epilogue, outside the candidate loops.
+// waits on LDS, so it wants as many waves as its registers allow; what is spilled for them (FP32
+// two-channel quad records: 12 to 18 values a lane, 50 MB of writes at 512^2) is the batch's
+// set-up and the epilogue, outside the candidate loops.  At 4 waves, without spills, the q
+// transpose takes 118 us against 101.6 at 512^2 and a plain one of 350 x 301 pixels 69 against
+// 54, but at 256^2 24.4 against 26.6 and at 1024^2 681 against 704.
 template <typename T, typename A, int W>
 constexpr int bp_min_waves() {
     if (sizeof(T) == 8) return W <= 2 ? 6 : W <= 4 ? 5 : W <= 8 ? 3 : 2;
